@@ -153,11 +153,25 @@ __device__ __forceinline__ double xexpm1_series(double x)
 // bm = 1.4 x2/(e^x2 - 1) = 1.4 x2 e^-x2/(1 - e^-x2); where |x| < 1/64 the
 // quotient is its series instead (the difference would cancel).  bh =
 // 4/(e^-x2 + 1).  The four denominators share one division as in
-// hh_rates_lib.  For |v| <= 1000 mV the powers stay far from overflow;
-// beyond (a neuron running away, or NaN) the library path is used.
-__device__ __forceinline__ HHRates hh_rates(double v)
+// hh_rates_lib.
+//
+// WIDE: any v.  For |v| <= 1000 mV the powers stay far from overflow; beyond
+// (a neuron running away, or NaN) the library path is used; where the product
+// of the denominators is not a finite nonzero number the lane divides four
+// times.  Not WIDE: |v| <= kHHNear, where the product lies within
+// [2^-20, 2^200], so neither check is needed and the division is its plain
+// Newton sequence without the scaling and fix-up steps of the general one
+// (the reciprocal is correctly rounded either way, so the bits are the same),
+// and the series are evaluated only in a wavefront with a lane that needs
+// one.  Both forms give the same bits wherever both apply.  Bound by issue and
+// by the dependent chain; measured against the wide form alone (neuron update
+// of 1 100, 21 000 and 1.12 M Traub-Miles neurons, launches stamped one by
+// one): 6.97 -> 6.35, 5.82 -> 5.31 and 31.1 -> 30.1 us, 92 -> 81 VGPRs.
+constexpr double kHHNear = 200.0;   // mV
+
+template <bool WIDE>
+__device__ __forceinline__ HHRates hh_rates_exp(double v)
 {
-    if (!(fabs(v) <= 1000.0)) return hh_rates_lib(v);
     constexpr double kE13 = 0x1.2f6053b981d98p-19;   // e^-13
     constexpr double kEm5 = 0x1.b993fe00d5376p-8;    // e^-5
     constexpr double kE10 = 0x1.7cd79b5647c9bp-15;   // e^-10
@@ -169,14 +183,30 @@ __device__ __forceinline__ HHRates hh_rates(double v)
     const double u2 = u * u, u4 = u2 * u2, u8 = u4 * u4, u16 = u8 * u8;
     const double u9 = u8 * u, u18 = u16 * u2, u20 = u16 * u4, u36 = u18 * u18, u72 = u36 * u36, u90 = u72 * u18;
     const double x1 = (-52.0 - v) * 0.25, x2 = (v + 25.0) * 0.2, x3 = (-50.0 - v) * 0.2;
-    const double e1 = kE13 * u90, em2 = kEm5 * u72, e3 = kE10 * u72;
+    const double em2 = kEm5 * u72;
     const bool s1 = fabs(x1) < kSmall, s2 = fabs(x2) < kSmall, s3 = fabs(x3) < kSmall;
-    const double f1 = s1 ? 1.0 : e1 - 1.0, f2 = s2 ? 1.0 : 1.0 - em2, f3 = s3 ? 1.0 : e3 - 1.0;
-    const double f4 = em2 + 1.0;
+    const bool any = WIDE || (__builtin_amdgcn_ballot_w64(s1) | __builtin_amdgcn_ballot_w64(s2) |
+                              __builtin_amdgcn_ballot_w64(s3)) != 0;
+    double f1 = fma(kE13, u90, -1.0), f2 = fma(-kEm5, u72, 1.0), f3 = fma(kE10, u72, -1.0);
+    const double f4 = fma(kEm5, u72, 1.0);
+    if (any) {
+        asm volatile("");    // a branch, not selects in every wavefront
+        f1 = s1 ? 1.0 : f1;
+        f2 = s2 ? 1.0 : f2;
+        f3 = s3 ? 1.0 : f3;
+    }
     const double p12 = f1 * f2, p123 = p12 * f3, prod = p123 * f4;
     double i1, i2, i3, i4;
-    if (isfinite(prod) && prod != 0.0) {
-        const double q = 1.0 / prod;
+    if (!WIDE || (isfinite(prod) && prod != 0.0)) {
+        double q;
+        if constexpr (WIDE) {
+            q = 1.0 / prod;
+        } else {
+            q = __builtin_amdgcn_rcp(prod);
+            q = fma(q, fma(-prod, q, 1.0), q);
+            q = fma(q, fma(-prod, q, 1.0), q);
+            q = fma(fma(-prod, q, 1.0), q, q);
+        }
         i4 = q * p123;
         const double q123 = q * f4;
         i3 = q123 * p12;
@@ -189,13 +219,32 @@ __device__ __forceinline__ HHRates hh_rates(double v)
         i3 = 1.0 / f3;
         i4 = 1.0 / f4;
     }
-    r.am = 1.28 * (s1 ? xexpm1_series(x1) : x1 * i1);
-    r.bm = 1.4 * (s2 ? xexpm1_series(x2) : x2 * em2 * i2);
-    r.an = 0.16 * (s3 ? xexpm1_series(x3) : x3 * i3);
+    double a1 = x1 * i1, a2 = x2 * em2 * i2, a3 = x3 * i3;
+    if (any) {
+        asm volatile("");
+        a1 = s1 ? xexpm1_series(x1) : a1;
+        a2 = s2 ? xexpm1_series(x2) : a2;
+        a3 = s3 ? xexpm1_series(x3) : a3;
+    }
+    r.am = 1.28 * a1;
+    r.bm = 1.4 * a2;
+    r.an = 0.16 * a3;
     r.bh = 4.0 * i4;
     r.ah = kAh * u20;
     r.bn = kBn * u9;
     return r;
+}
+
+__device__ __noinline__ HHRates hh_rates_wide(double v)
+{
+    if (!(fabs(v) <= 1000.0)) return hh_rates_lib(v);
+    return hh_rates_exp<true>(v);
+}
+
+__device__ __forceinline__ HHRates hh_rates(double v)
+{
+    if (!(fabs(v) <= kHHNear)) return hh_rates_wide(v);
+    return hh_rates_exp<false>(v);
 }
 
 // One forward-Euler substep, every right-hand side from the substep-start state.

@@ -816,3 +816,46 @@ def test_raster_replay_rms(snn, workload):
     assert rms["free"] <= 1e-3 and rms["replay"] <= 1e-3
     for net in (free, rep):
         net.close()
+
+
+def _rate_sums(v):
+    """alpha + beta of m, h and n at voltages v (mV)."""
+    def ratio(x):
+        with np.errstate(all="ignore"):
+            r = x / np.expm1(x)
+        return np.where(np.abs(x) < 1e-6, 1.0 - 0.5 * x, np.where(x > 700.0, 0.0, r))
+    with np.errstate(over="ignore"):
+        m = 1.28 * ratio((-52.0 - v) / 4.0) + 1.4 * ratio((v + 25.0) / 5.0)
+        h = 0.128 * np.exp((-48.0 - v) / 18.0) + 4.0 / (1.0 + np.exp((-25.0 - v) / 5.0))
+        n = 0.16 * ratio((-50.0 - v) / 5.0) + 0.5 * np.exp((-55.0 - v) / 40.0)
+    return m, h, n
+
+
+def test_rates_at_the_edges_of_their_forms(snn):
+    """One Euler substep at voltages on both sides of every line between the
+    forms of the rates (the near range's +-200 mV, the power form's +-1000 mV,
+    |x| = 1/64 of each removable singularity), with and without such lanes in
+    the same wavefront.  A gate's step is h (a (1 - x) - b x); the rates are
+    within 6e-13 relative of the oracle's and the pair holds 48 bits, so the
+    gates agree within 1e-12 (1 + h (a + b))."""
+    say("case: rates at the edges of their forms")
+    edges = [s * e for e in (200.0, 1000.0) for s in (-1.0, 1.0)]
+    edges += [c + s * w / 64.0 for c, w in ((-52.0, 4.0), (-25.0, 5.0), (-50.0, 5.0)) for s in (-1.0, 0.0, 1.0)]
+    at = np.array([x for e in edges for x in (np.nextafter(np.float32(e), -np.inf, dtype=np.float32), np.float32(e),
+                                              np.nextafter(np.float32(e), np.inf, dtype=np.float32))], np.float64)
+    plain = np.linspace(-100.3, 59.7, 64 * 3)                      # whole wavefronts without an edge lane
+    plain = plain[np.all([np.abs(plain - c) > 0.2 for c in (-52.0, -50.0, -25.0)], axis=0)][:128]
+    v = np.concatenate([plain, at, np.array([-900.0, -450.0, 333.0, 1500.0, -1200.0])])
+    inst = dict(g_scale=1.0, seed=1, pops=[dict(name="P", kind="hh", n=v.size, rate_hz=0.0, i_ext=0.0)], projs=[])
+    spec = dict(dt=0.02, substeps=1, instances=[inst])
+    net = snn.Network(spec)
+    orc = O.OracleNet(inst, dt=0.02, substeps=1)
+    for var, x in ((snn.V, v), (snn.M, np.full(v.size, 0.25)), (snn.H, np.full(v.size, 0.6)), (snn.N, np.full(v.size, 0.4))):
+        net.set_state(0, 0, var, x)
+        orc.set(0, var, net.state(0, 0, var))
+    net.step(1)
+    orc.step(1)
+    for var, s in zip((snn.M, snn.H, snn.N), _rate_sums(v)):
+        a, b = net.state(0, 0, var), orc.get(0, var)
+        assert np.all(np.abs(a - b) <= 1e-12 * (1.0 + 0.02 * s)), (var, v[np.argmax(np.abs(a - b) / (1.0 + 0.02 * s))])
+    net.close()
