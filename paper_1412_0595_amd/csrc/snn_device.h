@@ -14,12 +14,11 @@ __device__ __forceinline__ uint32_t philox_first_word(uint32_t x0, uint32_t x1, 
 {
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t a_lo = 0xD2511F53u * x0, a_hi = __umulhi(0xD2511F53u, x0);
-        const uint32_t b_lo = 0xCD9E8D57u * x2, b_hi = __umulhi(0xCD9E8D57u, x2);
-        x0 = b_hi ^ x1 ^ key0;
-        x1 = b_lo;
-        x2 = a_hi ^ x3 ^ key1;
-        x3 = a_lo;
+        const uint64_t pa = (uint64_t)0xD2511F53u * x0, pb = (uint64_t)0xCD9E8D57u * x2;
+        x0 = (uint32_t)(pb >> 32) ^ x1 ^ key0;
+        x1 = (uint32_t)pb;
+        x2 = (uint32_t)(pa >> 32) ^ x3 ^ key1;
+        x3 = (uint32_t)pa;
         key0 += 0x9E3779B9u;
         key1 += 0xBB67AE85u;
     }
@@ -247,21 +246,29 @@ __device__ __forceinline__ HHRates hh_rates(double v)
     return hh_rates_exp<false>(v);
 }
 
-// One forward-Euler substep, every right-hand side from the substep-start state.
-__device__ __forceinline__ void hh_substep(const Seg &S, double hs, double hc, double iin, double &v, double &m,
-                                           double &h, double &n)
+// One forward-Euler substep, every right-hand side from the substep-start
+// state; S holds the population's constants.  The part that the input current
+// does not enter: advances the gates and returns the ionic current (both at
+// the substep's start).  Contractions are written out, so that every kernel
+// rounds alike.
+template <class P>
+__device__ __forceinline__ double hh_gates(const P &S, double hs, double v, double &m, double &h, double &n)
 {
     const HHRates r = hh_rates(v);
     const double n2 = n * n;
-    const double iion = S.gna * (m * m * m * h) * (v - S.ena) + S.gk * (n2 * n2) * (v - S.ek) + S.gl * (v - S.el);
-    const double vn = v + hc * (iin - iion);
-    const double mn = m + hs * (r.am * (1.0 - m) - r.bm * m);
-    const double hn = h + hs * (r.ah * (1.0 - h) - r.bh * h);
-    const double nn = n + hs * (r.an * (1.0 - n) - r.bn * n);
-    v = vn;
-    m = mn;
-    h = hn;
-    n = nn;
+    const double iion = fma(S.gl, v - S.el, fma(S.gna * (m * m * m * h), v - S.ena, S.gk * (n2 * n2) * (v - S.ek)));
+    m = fma(hs, fma(1.0 - m, r.am, -(r.bm * m)), m);
+    h = fma(hs, fma(1.0 - h, r.ah, -(r.bh * h)), h);
+    n = fma(hs, fma(1.0 - n, r.an, -(r.bn * n)), n);
+    return iion;
+}
+
+template <class P>
+__device__ __forceinline__ void hh_substep(const P &S, double hs, double hc, double iin, double &v, double &m,
+                                           double &h, double &n)
+{
+    const double iion = hh_gates(S, hs, v, m, h, n);
+    v = fma(hc, iin - iion, v);
 }
 
 // Whether x stays finite once held in the fp32 state arrays: |x| below
@@ -282,10 +289,10 @@ constexpr double kIzhPeak = 30.0;   // mV
 
 __device__ __forceinline__ void izh_substep(double ia, double ib, double hs, double iin, double &v, double &u)
 {
-    const double dv = 0.04 * v * v + 5.0 * v + 140.0 - u + iin;
-    const double du = ia * (ib * v - u);
-    v = v + hs * dv;
-    u = u + hs * du;
+    const double dv = fma(5.0, v, 0.04 * v * v) + 140.0 - u + iin;
+    const double du = ia * fma(ib, v, -u);
+    v = fma(hs, dv, v);
+    u = fma(hs, du, u);
 }
 
 // A double held as an fp32 pair (hi = fl32(x), lo = fl32(x - hi)).

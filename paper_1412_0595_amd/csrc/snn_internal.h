@@ -329,6 +329,81 @@ struct LtpArgs {
     StepState *st;
 };
 
+// Resident stepping (snn_resident.hip): an instance's words dealt out over
+// the blocks of its cluster.
+constexpr int kResRing = 4;      // steps of spike words in the exchange ring (a power of two)
+constexpr int kResList = 1024;   // spiking rows a block lists in LDS for one step
+
+// A projection (or the part of it that ends in one block), as the block's
+// source of deliveries.
+struct ResFeed {
+    const int32_t *bounds;   // slice of pre row i: [bounds[i * stride], bounds[i * stride + 1])
+    int32_t stride;
+    int32_t syn;             // the projection's first synapse, from the instance's first
+    int32_t g0;              // LDS conductance index of post neuron 0 (may be negative)
+    int32_t word0;           // first word of the pre population, from the instance's first
+};
+
+struct ResWord {             // 64 neurons of one population
+    int64_t gw;              // global word
+    int32_t seg;
+    int32_t g_off[kMaxIn];   // LDS conductance index of each incoming projection's first neuron here
+    int32_t pad_;
+};
+
+struct ResBlock {
+    int32_t inst, n_blocks;  // blocks of the instance's cluster
+    int64_t w_first;         // first word of the instance
+    int32_t n_words;         // words of the instance
+    int32_t n_state, n_poi;  // words of this block with a membrane (first in its word list) and without
+    int32_t n_g, n_feed;     // LDS conductances, feeds
+    int64_t word0, feed0;    // this block's entries in the word and feed tables,
+    int64_t wfeed0;          // and in the table of each instance word's feeds
+    int64_t syn_first;       // first synapse of the instance
+    int64_t x_off;           // the instance's exchange ring
+};
+
+struct ResSplit {            // slice bounds to build: one split projection
+    int64_t rp_base, syn_base, out0, start0;
+    int32_t n_pre, parts;
+};
+
+struct ResArgs {
+    const Seg *segs;
+    const ResBlock *blocks;
+    const ResWord *words;
+    const ResFeed *feeds;
+    const uint32_t *wfeeds;  // per block and word of the instance: first feed << 16 | number of feeds
+    uint64_t *xbuf;          // per instance: [kResRing][words][2] of (tag, half word)
+    float *vh, *vl, *mh, *ml, *hh, *hl, *nh, *nl;
+    int64_t *G;
+    int32_t *counts;
+    double *vsum;
+    int32_t *nan_count;
+    uint64_t *bits;
+    int64_t n_waves;
+    uint64_t *raster;
+    int32_t raster_steps;
+    int32_t substeps;
+    double hs;
+    const int32_t *col_pool;
+    const float *w_pool;
+    const float *gscale;
+    const float4 *izp;
+    StepState *st;
+    int64_t t0, n;
+    uint32_t tag0;           // exchange tag of step t0
+    int32_t skip_first;      // 1: S(t0 - 1) is already in the conductances
+    int64_t max_wait;        // wall-clock ticks a block waits for its cluster's words
+};
+
+hipError_t launch_slice_bounds(const ResSplit &d, const int32_t *rp_pool, const int32_t *col_pool,
+                               const int32_t *starts, int32_t *out, hipStream_t s);
+// Whether the kernel runs with this block size and LDS, and (together) all
+// blocks are resident at once.
+bool resident_fits(int feat, int block, size_t lds, int blocks, bool together, int n_cu);
+hipError_t launch_resident(const ResArgs &a, int feat, int blocks, int block, size_t lds, bool together, hipStream_t s);
+
 // Reverse-time adjoint of one population's time-averaged voltage with the
 // spike raster held fixed (snn_adjoint.hip).  Loss neurons are numbered
 // compactly, instance-major: instance b owns [loss_base[b], loss_base[b+1]).

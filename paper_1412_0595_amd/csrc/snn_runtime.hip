@@ -133,6 +133,22 @@ struct HostProj {            // host copy of what state access needs
     double decay;                   // conductance decay per step
 };
 
+// Resident stepping: the words of every instance dealt out over blocks.
+struct ResidentPlan {
+    bool ok;                 // the network fits and is expected to step faster this way
+    bool on;                 // used by the steps (off: the launch shape was set by the caller, or measured faster)
+    int blocks, block;
+    size_t lds;
+    bool together;           // some cluster has several blocks: all must be resident (cooperative launch)
+    uint32_t tag;            // exchange tag of the next step taken this way
+    ResBlock *d_blocks;
+    ResWord *d_words;
+    ResFeed *d_feeds;
+    uint32_t *d_wfeeds;
+    int32_t *d_bounds;
+    uint64_t *d_xbuf;
+};
+
 struct snn_net {
     // configuration
     double dt;
@@ -238,6 +254,12 @@ struct snn_net {
     uint32_t *d_flag;
     uint32_t *d_wmax;        // per projection: bits of the largest weight (weight checks)
     int64_t max_nnz;
+
+    ResidentPlan res;
+    // The pending deliveries of S(t-1) are held by its spike words alone (as
+    // the resident steps leave them), not by the queues or the fused buffer.
+    bool pend_bits;
+    bool pend_delivered;     // they are already in G (a switch out of fused mode)
 
     // launch shape and captured step sequences: graphs[k] replays
     // graph_len[k] whole steps (kGraphSteps, and the remainders asked for)
@@ -488,12 +510,92 @@ int prepare_graphs(snn_net *net, int64_t n)
     return rc;
 }
 
-// n steps as replays of captured graphs: n div 64 of the 64-step graph, then
-// one graph of the remaining n mod 64 steps.
+int materialize(snn_net *net);
+
+constexpr int64_t kResidentMin = 8;        // steps in a call that are worth a cooperative launch
+constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
+
+// Whether a call of n steps runs resident.  A cooperative launch costs more
+// than the graph replay of a few steps, but less than laying out the pending
+// work again.
+bool use_resident(snn_net *net, int64_t n)
+{
+    if (!net->res.on || n < 1) return false;
+    if (net->res.together && n < kResidentMin && !net->pend_bits) return false;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(net->stream, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c == hipStreamCaptureStatusNone;
+}
+
+// The pending deliveries are from here on those of the spike words of
+// S(t-1): what the fused buffer holds of them is dropped.
+int pending_to_bits(snn_net *net)
+{
+    if (net->pend_bits) return SNN_OK;
+    if (net->launch.mode == kModeFused)
+        HIP_OK(launch_fill_zero(net->D, 2 * 8 * (size_t)net->G_count, net->stream));
+    net->pend_bits = true;
+    return SNN_OK;
+}
+
+int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps)
+{
+    int rc = pending_to_bits(net);
+    if (rc) return rc;
+    const NeuronArgs na = neuron_args(net);
+    ResArgs a{};
+    a.segs = net->d_segs;
+    a.blocks = net->res.d_blocks;
+    a.words = net->res.d_words;
+    a.feeds = net->res.d_feeds;
+    a.wfeeds = net->res.d_wfeeds;
+    a.xbuf = net->res.d_xbuf;
+    a.vh = net->vh; a.vl = net->vl; a.mh = net->mh; a.ml = net->ml;
+    a.hh = net->hh; a.hl = net->hl; a.nh = net->nh; a.nl = net->nl;
+    a.G = net->G;
+    a.counts = net->counts;
+    a.vsum = net->vsum;
+    a.nan_count = net->nan_count;
+    a.bits = net->bits;
+    a.n_waves = net->n_waves;
+    a.raster = raster;
+    a.raster_steps = raster_steps;
+    a.substeps = net->substeps;
+    a.hs = na.hs;
+    a.col_pool = net->d_col;
+    a.w_pool = net->d_w;
+    a.gscale = net->d_gscale;
+    a.izp = net->d_izp;
+    a.st = net->st;
+    a.max_wait = (int64_t)20 * 100000000;   // 20 s of the 100 MHz wall clock
+    while (n > 0) {
+        a.t0 = net->t;
+        a.n = std::min(n, kResidentLaunch);
+        a.tag0 = net->res.tag;
+        a.skip_first = net->pend_delivered ? 1 : 0;
+        HIP_OK(launch_resident(a, na.feat, net->res.blocks, net->res.block, net->res.lds, net->res.together,
+                               net->stream));
+        net->res.tag += (uint32_t)a.n;
+        net->pend_delivered = false;
+        net->t += a.n;
+        n -= a.n;
+    }
+    return SNN_OK;
+}
+
+// n steps: resident, or as replays of captured graphs (n div 64 of the
+// 64-step graph, then one graph of the remaining n mod 64 steps).
 int run_steps(snn_net *net, int64_t n)
 {
-    int rc = prepare_graphs(net, n);
+    if (use_resident(net, n))
+        return run_resident(net, n, net->raster_steps > 0 ? net->raster : nullptr, std::max(net->raster_steps, 1));
+    int rc = n > 0 ? materialize(net) : SNN_OK;
+    if (!rc) rc = prepare_graphs(net, n);
     if (rc) return rc;
+    if (n > 0) net->pend_delivered = false;
     hipGraphExec_t g = nullptr;
     if (n >= kGraphSteps) {
         if ((rc = graph_for(net, kGraphSteps, &g))) return rc;
@@ -664,6 +766,7 @@ static int timed_on_snapshot(snn_net *net, F body, double *ms_out)
         return fail(SNN_ENOMEM, "snapshot allocation failed");
     }
     const int64_t t_saved = net->t;
+    const bool bits_saved = net->pend_bits, delivered_saved = net->pend_delivered;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = SNN_OK;
     hipError_t e = hipMemcpyAsync(snap, net->d_arena, (size_t)net->arena_bytes, hipMemcpyDeviceToDevice, net->stream);
@@ -680,6 +783,8 @@ static int timed_on_snapshot(snn_net *net, F body, double *ms_out)
     if (e == hipSuccess && rc == SNN_OK && wsnap) e = hipMemcpyAsync(net->d_w, wsnap, 4 * (size_t)net->w_count, hipMemcpyDeviceToDevice, net->stream);
     if (e == hipSuccess && rc == SNN_OK) e = hipStreamSynchronize(net->stream);
     net->t = t_saved;
+    net->pend_bits = bits_saved;
+    net->pend_delivered = delivered_saved;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(snap);
@@ -710,6 +815,7 @@ void snn_default_hh(double *p)
 const char *snn_last_error(void) { return g_err.c_str(); }
 
 static int update_qbuckets(snn_net *net);
+static int plan_resident(snn_net *net);
 
 int snn_create(const snn_config *cfg, snn_net **out)
 {
@@ -1329,6 +1435,7 @@ int snn_create(const snn_config *cfg, snn_net **out)
         return bail(fail(SNN_EDEVICE, "device synchronisation failed"));
     }
     if ((rc = update_qbuckets(net))) return bail(rc);
+    if ((rc = plan_resident(net))) return bail(rc);
     net->t = 0;
     *out = net;
     if (cfg->autotune) {
@@ -1367,7 +1474,8 @@ int snn_sync(snn_net *net)
     HIP_OK(hipMemcpy(&st, net->st, sizeof st, hipMemcpyDeviceToHost));
     if (st.overflow) {
         net->sticky = true;
-        return fail(SNN_EDEVICE, "work queue overflow (flag %u)", st.overflow);
+        return (st.overflow & 4u) ? fail(SNN_EDEVICE, "a block of a resident step waited too long for its cluster")
+                                  : fail(SNN_EDEVICE, "work queue overflow (flag %u)", st.overflow);
     }
     return SNN_OK;
 }
@@ -1525,6 +1633,271 @@ int snn_get_last_spikes(snn_net *net, int32_t inst, int32_t pop, uint8_t *out)
     return SNN_OK;
 }
 
+// ------------------------------ resident plan --------------------------------
+// Deals the words of every instance out over the blocks of its cluster and
+// builds the blocks' tables.  More blocks shorten the update (four words, one
+// per SIMD, take 1.9 us; each further word on a SIMD 0.9) and lengthen the
+// exchange (0.9 us and 4 ns per word of the instance, measured), so the words
+// per block are chosen by that estimate, over all sizes whose blocks are
+// resident together at one per CU; a network of more instances than that
+// keeps each in one block, any number of them.  Networks that do not fit (LDS:
+// 2.6 to 4 KiB per word), with plastic projections, or whose estimate is not
+// below the step kernels' (7 us and 2.5 ns per word, measured on batches of 20 to
+// 256 instances) keep the step kernels.
+static int plan_resident(snn_net *net)
+{
+    ResidentPlan &R = net->res;
+    R = ResidentPlan{};
+    R.tag = 1;
+    if (net->plastic || net->n_waves == 0) return SNN_OK;
+    const int feat = neuron_args(net).feat;
+    hipDeviceProp_t prop{};
+    if (hipGetDeviceProperties(&prop, net->device) != hipSuccess) {
+        (void)hipGetLastError();
+        return SNN_OK;
+    }
+    const int n_cu = prop.multiProcessorCount;
+    constexpr int64_t kLds = 156 * 1024;
+
+    struct Inst { int64_t w_first, n_words, n_state, n_poi, syn_first, nnz; double load; };
+    std::vector<Inst> in(net->n_inst);
+    double step_kernels = 7.0;
+    for (int b = 0; b < net->n_inst; ++b) {
+        Inst &I = in[b];
+        I = Inst{};
+        if (net->seg_of[b].empty()) return SNN_OK;
+        I.w_first = net->segs[net->seg_of[b][0]].base / kWave;
+        for (int s : net->seg_of[b]) {
+            const Seg &S = net->segs[s];
+            const int64_t w = align_up(S.n, kWave) / kWave;
+            I.n_words += w;
+            (S.kind == kPoisson ? I.n_poi : I.n_state) += w;
+            I.load += (double)w * (S.kind == kHH ? 1.0 : 0.3);
+            step_kernels += 0.0025 * (double)w * (S.kind == kHH ? 1.0 : 0.3);
+        }
+        for (size_t k = 0; k < net->proj_of[b].size(); ++k) {
+            const Proj &P = net->projs[net->proj_of[b][k]];
+            if (k == 0) I.syn_first = P.syn_base;
+            I.nnz += P.nnz;
+        }
+        if (I.n_words == 0 || I.n_words > ((int64_t)1 << 20) || I.nnz >= ((int64_t)1 << 31)) return SNN_OK;
+    }
+
+    // words of segment `s` held by each block of its cluster
+    struct Layout {
+        int64_t blocks = 0;
+        std::vector<int> first, n;                       // per instance: first block, blocks
+        std::vector<std::vector<int32_t>> share;         // per segment: words per block of the cluster
+        std::vector<int64_t> state, poi, lds;            // per block
+        double cost = 0.0;
+    };
+    auto lay_out = [&](double per_block) {
+        Layout L;
+        L.share.resize(net->segs.size());
+        int64_t worst_lds = 0;
+        double worst = 0.0;
+        bool split = false;
+        for (int b = 0; b < net->n_inst; ++b) {
+            const Inst &I = in[b];
+            const int M = (int)std::min<int64_t>(std::max<int64_t>(1, (int64_t)std::ceil(I.load / per_block)), I.n_words);
+            L.first.push_back((int)L.blocks);
+            L.n.push_back(M);
+            std::vector<double> load(M, 0.0);
+            std::vector<int64_t> st(M, 0), po(M, 0), g(M, 0), feeds(M, 0);
+            std::vector<int> segs(net->seg_of[b].begin(), net->seg_of[b].end());
+            std::stable_sort(segs.begin(), segs.end(), [&](int x, int y) {
+                return std::make_pair(net->segs[x].kind == kPoisson, -net->segs[x].n) <
+                       std::make_pair(net->segs[y].kind == kPoisson, -net->segs[y].n);
+            });
+            for (int s : segs) {
+                // equal parts, the remainder to the least loaded blocks
+                const Seg &S = net->segs[s];
+                const int64_t w = align_up(S.n, kWave) / kWave;
+                const double c = S.kind == kHH ? 1.0 : 0.3;
+                std::vector<int32_t> &sh = L.share[s];
+                sh.assign(M, (int32_t)(w / M));
+                std::vector<int> order(M);
+                for (int r = 0; r < M; ++r) order[r] = r;
+                std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return load[x] < load[y]; });
+                for (int64_t r = 0; r < w % M; ++r) sh[order[r]]++;
+                for (int r = 0; r < M; ++r) {
+                    load[r] += c * sh[r];
+                    (S.kind == kPoisson ? po[r] : st[r]) += sh[r];
+                    if (sh[r] == 0) continue;
+                    g[r] += (int64_t)S.n_in * sh[r] * kWave;
+                    for (int q = 0; q < S.n_in; ++q) {
+                        const Proj &P = net->projs[S.in_proj[q]];
+                        if (P.nnz == 0) continue;
+                        feeds[r]++;
+                    }
+                }
+            }
+            const double exchange = M > 1 ? 0.9 + 0.004 * (double)I.n_words : 0.0;
+            split |= M > 1;
+            for (int r = 0; r < M; ++r) {
+                if (feeds[r] >= (1 << 16)) return L.blocks = 0, L;
+                L.state.push_back(st[r]);
+                L.poi.push_back(po[r]);
+                L.lds.push_back(24 * g[r] + 20 * I.n_words + 12 * kResList + ((feat & kFeatRec) ? 3072 : 2560) * st[r] +
+                                (int64_t)sizeof(ResFeed) * feeds[r]);
+                worst_lds = std::max(worst_lds, L.lds.back());
+                const double rounds = std::ceil((double)st[r] / 16.0), src = 0.35 * std::ceil((double)po[r] / 16.0);
+                const double t = 1.5 * rounds + std::max(exchange, 0.8 * rounds + src) + 1.0;
+                worst = std::max(worst, t);
+            }
+            L.blocks += M;
+        }
+        const int64_t fit = std::min<int64_t>(kLds / std::max<int64_t>(worst_lds, 1), 4);
+        if (fit < 1 || (split && L.blocks > n_cu)) return L.blocks = 0, L;
+        // blocks beyond one per CU share it, beyond what fits they follow one another
+        L.cost = worst * (double)((L.blocks + n_cu - 1) / n_cu);
+        return L;
+    };
+    Layout best;
+    for (double per : {4.0, 5.0, 6.0, 7.0, 8.0, 10.0, 12.0, 14.0, 16.0, 20.0, 24.0, 28.0, 32.0, 40.0, 48.0, 64.0}) {
+        Layout L = lay_out(per);
+        if (L.blocks > 0 && (best.blocks == 0 || L.cost < best.cost)) best = std::move(L);
+    }
+    if (best.blocks == 0 || best.cost > step_kernels) return SNN_OK;
+
+    // ---- the tables
+    std::vector<ResBlock> blocks;
+    std::vector<ResWord> words;
+    std::vector<ResFeed> feeds;
+    std::vector<int64_t> feed_bounds;        // offset into the built bounds, -1: the row pointers
+    std::vector<uint32_t> wfeeds;
+    std::vector<ResSplit> splits;
+    std::vector<int32_t> starts;             // first neuron of each part of each split projection
+    int64_t x_total = 0, bounds_total = 0, max_lds = 0, max_state = 0;
+    for (int b = 0; b < net->n_inst; ++b) {
+        const Inst &I = in[b];
+        const int M = best.n[b];
+        std::vector<int64_t> built(net->proj_of[b].size() + 1, -1);
+        for (int r = 0; r < M; ++r) {
+            ResBlock B{};
+            B.inst = b;
+            B.n_blocks = M;
+            B.w_first = I.w_first;
+            B.n_words = (int32_t)I.n_words;
+            B.word0 = (int64_t)words.size();
+            B.wfeed0 = (int64_t)wfeeds.size();
+            B.feed0 = (int64_t)feeds.size();
+            B.syn_first = I.syn_first;
+            B.x_off = x_total;
+            std::vector<int> pre;                         // pre population of each of its feeds
+            for (int pass = 0; pass < 2; ++pass)          // words with a membrane first
+                for (int s : net->seg_of[b]) {
+                    const Seg &S = net->segs[s];
+                    if ((S.kind == kPoisson) != (pass == 1)) continue;
+                    const std::vector<int32_t> &sh = best.share[s];
+                    if (sh[r] == 0) continue;
+                    int64_t w0 = 0;
+                    int part = 0, parts = 0;
+                    for (int k = 0; k < M; ++k) {
+                        if (k < r) w0 += sh[k], part += sh[k] > 0;
+                        parts += sh[k] > 0;
+                    }
+                    std::vector<int64_t> g0(S.n_in);
+                    for (int q = 0; q < S.n_in; ++q) {
+                        const Proj &P = net->projs[S.in_proj[q]];
+                        g0[q] = B.n_g;
+                        B.n_g += sh[r] * kWave;
+                        if (P.nnz == 0) continue;
+                        ResFeed F{};
+                        F.stride = parts > 1 ? parts + 1 : 1;
+                        F.syn = (int32_t)(P.syn_base - I.syn_first);
+                        F.g0 = (int32_t)(g0[q] - w0 * kWave);
+                        F.word0 = (int32_t)(net->segs[P.pre_seg].base / kWave - I.w_first);
+                        int64_t off = -1;
+                        if (parts > 1) {
+                            int64_t &at = built[std::find(net->proj_of[b].begin(), net->proj_of[b].end(), S.in_proj[q]) -
+                                                net->proj_of[b].begin()];
+                            if (at < 0) {
+                                at = bounds_total;
+                                splits.push_back(ResSplit{P.rp_base, P.syn_base, at, (int64_t)starts.size(), P.n_pre, parts});
+                                int64_t w = 0;
+                                for (int k = 0; k < M; ++k)
+                                    if (sh[k] > 0) {
+                                        starts.push_back((int32_t)(w * kWave));
+                                        w += sh[k];
+                                    }
+                                starts.push_back(INT32_MAX);
+                                bounds_total += (int64_t)P.n_pre * (parts + 1);
+                            }
+                            off = at + part;
+                        }
+                        feed_bounds.push_back(off >= 0 ? off : -1 - P.rp_base);
+                        pre.push_back(P.pre_seg);
+                        feeds.push_back(F);
+                        B.n_feed++;
+                    }
+                    for (int32_t k = 0; k < sh[r]; ++k) {
+                        ResWord W{};
+                        W.gw = S.base / kWave + w0 + k;
+                        W.seg = s;
+                        for (int q = 0; q < S.n_in; ++q) W.g_off[q] = (int32_t)(g0[q] + (int64_t)k * kWave);
+                        words.push_back(W);
+                        (pass == 0 ? B.n_state : B.n_poi)++;
+                    }
+                }
+            // the block's feeds by pre population, and each word's among them
+            std::vector<int> by(B.n_feed);
+            for (int k = 0; k < B.n_feed; ++k) by[k] = k;
+            std::stable_sort(by.begin(), by.end(), [&](int x, int y) { return pre[x] < pre[y]; });
+            const std::vector<ResFeed> f(feeds.begin() + B.feed0, feeds.end());
+            const std::vector<int64_t> fb(feed_bounds.begin() + B.feed0, feed_bounds.end());
+            wfeeds.resize(B.wfeed0 + I.n_words, 0u);
+            for (int k = 0; k < B.n_feed; ++k) {
+                feeds[B.feed0 + k] = f[by[k]];
+                feed_bounds[B.feed0 + k] = fb[by[k]];
+                const Seg &S = net->segs[pre[by[k]]];
+                for (int64_t w = 0; w < align_up(S.n, kWave) / kWave; ++w) {
+                    uint32_t &e = wfeeds[B.wfeed0 + f[by[k]].word0 + w];
+                    if (e == 0) e = (uint32_t)k << 16;
+                    ++e;
+                }
+            }
+            max_state = std::max<int64_t>(max_state, B.n_state);
+            blocks.push_back(B);
+        }
+        if (M > 1) x_total += (int64_t)kResRing * 2 * I.n_words;
+        R.together |= M > 1;
+    }
+    for (int64_t l : best.lds) max_lds = std::max(max_lds, l);
+    R.blocks = (int)best.blocks;
+    R.block = kWave * (int)std::min<int64_t>(16, std::max<int64_t>(8, align_up(max_state, 4)));
+    R.lds = (size_t)align_up(max_lds, 256);
+    if (!resident_fits(feat, R.block, R.lds, R.blocks, R.together, n_cu)) return SNN_OK;
+    // single blocks end at their own times: the longest first
+    if (!R.together)
+        std::stable_sort(blocks.begin(), blocks.end(), [](const ResBlock &x, const ResBlock &y) {
+            return 3 * x.n_state + x.n_poi > 3 * y.n_state + y.n_poi;
+        });
+    R.d_blocks = (ResBlock *)dev_alloc(net, sizeof(ResBlock) * blocks.size());
+    R.d_words = (ResWord *)dev_alloc(net, sizeof(ResWord) * words.size());
+    R.d_feeds = (ResFeed *)dev_alloc(net, sizeof(ResFeed) * std::max<size_t>(feeds.size(), 1));
+    R.d_wfeeds = (uint32_t *)dev_alloc(net, 4 * std::max<size_t>(wfeeds.size(), 1));
+    R.d_bounds = (int32_t *)dev_alloc(net, 4 * (size_t)std::max<int64_t>(bounds_total, 1));
+    R.d_xbuf = (uint64_t *)dev_alloc(net, 8 * (size_t)std::max<int64_t>(x_total, 1));
+    int32_t *d_starts = (int32_t *)dev_alloc(net, 4 * std::max<size_t>(starts.size(), 1));
+    if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_bounds || !R.d_xbuf || !d_starts)
+        return fail(SNN_ENOMEM, "device allocation failed");
+    for (size_t k = 0; k < feeds.size(); ++k)
+        feeds[k].bounds = feed_bounds[k] >= 0 ? R.d_bounds + feed_bounds[k] : net->d_rp + (-1 - feed_bounds[k]);
+    int rc;
+    if ((rc = h2d(net, R.d_blocks, blocks.data(), sizeof(ResBlock) * blocks.size()))) return rc;
+    if ((rc = h2d(net, R.d_words, words.data(), sizeof(ResWord) * words.size()))) return rc;
+    if ((rc = h2d(net, R.d_feeds, feeds.data(), sizeof(ResFeed) * feeds.size()))) return rc;
+    if ((rc = h2d(net, R.d_wfeeds, wfeeds.data(), 4 * wfeeds.size()))) return rc;
+    if ((rc = h2d(net, d_starts, starts.data(), 4 * starts.size()))) return rc;
+    HIP_OK(launch_fill_zero(R.d_xbuf, 8 * (size_t)std::max<int64_t>(x_total, 1), net->stream));
+    for (const ResSplit &d : splits)
+        HIP_OK(launch_slice_bounds(d, net->d_rp, net->d_col, d_starts, R.d_bounds, net->stream));
+    HIP_OK(hipStreamSynchronize(net->stream));
+    R.ok = R.on = true;
+    return SNN_OK;
+}
+
 // Bucket offsets of the queue slots for the current block size and mode:
 // block b of the neuron update reserves in bucket b mod kQBuckets, sized to
 // the worst case of its waves' neurons.
@@ -1559,6 +1932,7 @@ static int rebuild_pending(snn_net *net, int ltp_seg, const uint8_t *ltp_flags)
 {
     int rc;
     const int slot = (int)((net->t + 1) & 1);
+    net->pend_delivered = false;
     StepState st;
     if ((rc = d2h(net, &st, net->st, sizeof st))) return rc;
     std::vector<uint64_t> all(net->n_waves);
@@ -1692,6 +2066,7 @@ static int leave_fused(snn_net *net)
         if ((rc = h2d(net, net->D + dslot * n, d.data(), 8 * (size_t)n))) return rc;
     }
     if ((rc = clear_queues(net))) return rc;
+    net->pend_delivered = true;
     const size_t nseg = net->segs.size();
     std::vector<uint32_t> zero(2 * nseg, 0);
     if ((rc = h2d(net, net->awcnt, zero.data(), 4 * zero.size()))) return rc;
@@ -1725,6 +2100,36 @@ static int deliver_queued_to_fused(snn_net *net, int mode)
     return clear_queues(net);
 }
 
+}  // extern "C"
+
+namespace {
+
+// Lays out the pending deliveries of S(t-1), where its spike words alone
+// hold them, as the current mode's step kernels take them.
+int materialize(snn_net *net)
+{
+    if (!net->pend_bits) return SNN_OK;
+    if (net->pend_delivered) {
+        // nothing is pending: empty queues, as the switch out of fused mode left them
+        const int rc = clear_queues(net);
+        if (!rc) net->pend_bits = false;
+        return rc;
+    }
+    int rc = clear_queues(net);
+    if (rc) return rc;
+    const int mode = net->launch.mode;
+    if (mode == kModeFused) net->launch.mode = kModeRows;
+    rc = rebuild_pending(net, -1, nullptr);
+    net->launch.mode = mode;
+    if (!rc && mode == kModeFused) rc = deliver_queued_to_fused(net, kModeRows);
+    if (!rc) net->pend_bits = false;
+    return rc;
+}
+
+}  // namespace
+
+extern "C" {
+
 // Replace S(t-1) of one population: rewrite its bitmask words and rebuild
 // the pending work (propagation of every population, potentiation of this
 // population's columns).
@@ -1742,6 +2147,13 @@ int snn_set_last_spikes(snn_net *net, int32_t inst, int32_t pop, const uint8_t *
     for (int i = 0; i < S.n; ++i)
         if (in[i]) words[i / kWave] |= (uint64_t)1 << (i % kWave);
     if ((rc = h2d(net, net->bits + slot * net->n_waves + S.base / kWave, words.data(), 8 * (size_t)nw))) return rc;
+    if (net->res.on) {
+        // the resident steps deliver from the words themselves
+        if ((rc = pending_to_bits(net))) return rc;
+        net->pend_delivered = false;
+        return SNN_OK;
+    }
+    if ((rc = materialize(net))) return rc;
     if (net->launch.mode != kModeFused) return rebuild_pending(net, s, in);
     // fused mode: the pending deliveries become those of the new S(t-1) of
     // every population, laid out as a rows-mode queue and run into the slot
@@ -1804,7 +2216,7 @@ int snn_set_gscale(snn_net *net, const float *per_instance)
     if ((rc = check_range(net, bound, wbound, per_instance))) return rc;
     std::copy(per_instance, per_instance + net->n_inst, net->gscale.begin());
     if ((rc = h2d(net, net->d_gscale, per_instance, 4 * (size_t)net->n_inst))) return rc;
-    if (net->launch.mode != kModeFused) return SNN_OK;
+    if (net->launch.mode != kModeFused || net->pend_bits) return SNN_OK;
     // fused mode: the pending deliveries of S(t-1) were made with the old
     // g_scale; the other modes deliver them at step t with the new one
     net->launch.mode = kModeRows;
@@ -1861,7 +2273,13 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
         return fail(SNN_EINVAL, "mode 2 (fused) needs a network without plastic projections");
     const snn_launch prev = net->launch;
     net->launch = *in;
+    net->res.on = false;      // a shape given by the caller is the one that runs
     if ((rc = update_qbuckets(net))) return rc;
+    if (net->pend_bits) {
+        if ((rc = materialize(net))) return rc;
+        drop_graphs(net);
+        return SNN_OK;
+    }
     // The pending work of the next step was laid out for the old mode and in
     // the buckets of the old block size: it is laid out again from the spike
     // bitmasks, contiguously (entering fused mode: as rows work, run at once
@@ -1889,7 +2307,7 @@ int snn_time_steps(snn_net *net, int64_t n_steps, double *out_ms)
     if (rc) return rc;
     if (n_steps < 1 || !out_ms) return fail(SNN_EINVAL, "need n_steps >= 1 and an output");
     // capture the graph before the clock starts: host capture time is not step time
-    if ((rc = prepare_graphs(net, n_steps))) return rc;
+    if (!use_resident(net, n_steps) && ((rc = materialize(net)) || (rc = prepare_graphs(net, n_steps)))) return rc;
     double ms = 0.0;
     rc = timed_on_snapshot(net, [&]() { return run_steps(net, n_steps); }, &ms);
     if (rc) return rc;
@@ -1906,6 +2324,7 @@ int snn_time_kernel(snn_net *net, int32_t which, int64_t launches, double *ms_pe
     if (which == 0 && net->launch.mode == kModeFused)
         return fail(SNN_ESTATE, "mode 2 (fused) has no propagation kernel");
     if (launches < 1 || launches > 1000000 || !ms_per_launch) return fail(SNN_EINVAL, "need 1 <= launches <= 1e6 and an output");
+    if ((rc = materialize(net))) return rc;
     PropArgs p = prop_args(net);
     LtpArgs l = ltp_args(net);
     NeuronArgs a = neuron_args(net);
@@ -1933,6 +2352,8 @@ int snn_profile_steps(snn_net *net, int64_t n_steps, double *ms_total, int64_t *
     if (rc) return rc;
     if (n_steps < 1 || n_steps > 100000 || !ms_total || !launches)
         return fail(SNN_EINVAL, "need 1 <= n_steps <= 100000 and two output arrays");
+    if ((rc = materialize(net))) return rc;
+    net->pend_delivered = false;
     const bool fused = net->launch.mode == kModeFused;
     const int per_step = fused ? 1 : net->plastic ? 3 : 2;
     std::vector<hipEvent_t> ev((size_t)(2 * per_step * n_steps), nullptr);
@@ -1985,6 +2406,7 @@ int snn_reset(snn_net *net)
     HIP_OK(hipMemcpyAsync(net->vh, net->d_init_state, 4 * 8 * (size_t)net->n_neurons_padded, hipMemcpyDeviceToDevice,
                           net->stream));
     net->t = 0;
+    net->pend_bits = net->pend_delivered = false;
     return SNN_OK;
 }
 
@@ -2052,7 +2474,7 @@ int snn_set_weights_device(snn_net *net, const float *src)
     HIP_OK(hipMemcpyAsync(net->d_w, src, 4 * (size_t)net->w_count, hipMemcpyDeviceToDevice, net->stream));
     HIP_OK(launch_gather_weights(net->d_w, net->d_pull_perm, (float *)net->d_pull_w, 4 * kWave * net->pull_count,
                                  net->stream));
-    if (net->launch.mode != kModeFused) return SNN_OK;
+    if (net->launch.mode != kModeFused || net->pend_bits) return SNN_OK;
     // fused mode: the pending deliveries of S(t-1) were made with the old
     // weights; the other modes deliver them at step t with the new ones
     net->launch.mode = kModeRows;
@@ -2141,6 +2563,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     na.raster = net->d_rec_raster;
     na.raster_steps = (int32_t)T;
     const PropArgs pa = prop_args(net);
+    const bool resident = use_resident(net, K);
     for (int64_t t = 0; t < T; ++t) {
         if (t % K == 0) {
             const int64_t sgi = t / K;
@@ -2148,6 +2571,12 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
                                   net->stream));
             HIP_OK(hipMemcpyAsync(net->d_ckpt_G + sgi * std::max<int64_t>(net->G_count, 1), net->G,
                                   8 * (size_t)net->G_count, hipMemcpyDeviceToDevice, net->stream));
+        }
+        if (resident) {
+            const int64_t k = std::min(K, T - t);
+            if ((rc = run_resident(net, k, net->d_rec_raster, (int32_t)T))) return rc;
+            t += k - 1;
+            continue;
         }
         HIP_OK(launch_propagate(pa, net->launch.prop_blocks, net->launch.prop_block, net->stream));
         HIP_OK(launch_neuron(na, net->launch.neuron_block, net->stream));
@@ -2356,10 +2785,18 @@ int snn_autotune_internal(snn_net *net, const char *cache)
 {
     const std::string sig = signature(net);
     snn_launch best = net->launch;
-    if (cache_lookup(cache, sig, &best)) return snn_set_launch(net, &best);
+    int rc;
+    if (cache_lookup(cache, sig, &best)) {
+        if ((rc = snn_set_launch(net, &best))) return rc;
+        net->res.on = net->res.ok;
+        return SNN_OK;
+    }
     const int64_t steps = 3 * kGraphSteps;
-    double best_ms = 0.0;
-    int rc = snn_time_steps(net, steps, &best_ms);   // also warms up
+    double best_ms = 0.0, resident_ms = 0.0;
+    if (net->res.on && (rc = snn_time_steps(net, steps, &resident_ms))) return rc;   // (warm-up)
+    if (net->res.on && (rc = snn_time_steps(net, steps, &resident_ms))) return rc;
+    net->res.on = false;
+    rc = snn_time_steps(net, steps, &best_ms);   // also warms up
     if (rc) return rc;
     if ((rc = snn_time_steps(net, steps, &best_ms))) return rc;
     // modes: rows, tiles, fused (no plastic projections), grouped (some projection to group)
@@ -2390,6 +2827,7 @@ int snn_autotune_internal(snn_net *net, const char *cache)
         best = cur_best;
     }
     if ((rc = snn_set_launch(net, &best))) return rc;
+    net->res.on = net->res.ok && resident_ms < best_ms;
     cache_store(cache, sig, best);
     return SNN_OK;
 }

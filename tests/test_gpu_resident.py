@@ -1,0 +1,140 @@
+"""Resident stepping against the step kernels: the steps that a network takes
+by default are bitwise those of an explicitly chosen launch shape, over the
+splits of its words that the plan can make, and pending work survives every
+change between the two."""
+import numpy as np
+import pytest
+
+from paper_1412_0595_amd import netgen
+
+pytestmark = pytest.mark.gpu
+
+MODES = (dict(mode=0), dict(mode=1), dict(mode=2), dict(mode=3))
+
+
+@pytest.fixture(scope="module")
+def snn():
+    from paper_1412_0595_amd import snn as s
+    s.load()
+    return s
+
+
+def layered(n, a, b, c, p_bc=0.5, rate=40.0):
+    rng = np.random.default_rng(11)
+    return dict(dt=0.1, substeps=3, instances=[
+        netgen.layered_instance(rng, a + 3 * i, b + 70 * i, c + i, rate_hz=rate, p_ab=0.3, p_bc=p_bc,
+                                seed=netgen.instance_seed(11, i)) for i in range(n)])
+
+
+def izhikevich():
+    return dict(dt=0.1, substeps=3, instances=[
+        netgen.izhikevich_instance(100, n_exc=241, n_inh=63, seed=netgen.instance_seed(5, i), conn_seed=5 + i)
+        for i in range(3)])
+
+
+# one block; a few; the blocks of 64-neuron parts and of odd remainders; many
+# single blocks (more than the device has compute units); two neuron models
+NETS = {
+    "tiny": lambda: layered(1, 5, 7, 3, 1.0),
+    "word_edges": lambda: layered(1, 64, 128, 65),
+    "small": lambda: layered(1, 100, 1000, 100, 1.0),
+    "split": lambda: layered(1, 300, 6001, 257),
+    "uneven": lambda: layered(5, 130, 500, 40),
+    "many": lambda: layered(300, 20, 40, 5),
+    "izh": izhikevich,
+}
+
+
+def everything(net, spec):
+    """All state that the steps leave, as one list of arrays."""
+    out = [net.nan_counts()]
+    for b, inst in enumerate(spec["instances"]):
+        for p, pop in enumerate(inst["pops"]):
+            out += [net.spikes(b, p), net.last_spikes(b, p)]
+            if pop["kind"] != "poisson":
+                out += [net.state(b, p, v) for v in range(2 if pop["kind"] == "izh" else 4)]
+        out += [net.conductance(b, q) for q in range(len(inst["projs"]))]
+    return out
+
+
+def differing(x, y):
+    """Indexes of the arrays that differ."""
+    assert len(x) == len(y)
+    return [k for k, (a, b) in enumerate(zip(x, y)) if not np.array_equal(a, b, equal_nan=a.dtype.kind == "f")]
+
+
+def by_modes(snn, spec, mode, run):
+    net = snn.Network(spec)
+    net.set_launch(**mode)
+    run(net)
+    out = everything(net, spec)
+    net.close()
+    return out
+
+
+@pytest.mark.parametrize("name", list(NETS))
+def test_default_steps_equal_the_step_kernels(snn, name):
+    print(f"case: resident {name}", flush=True)
+    spec = NETS[name]()
+
+    def run(net):
+        for n in (1, 30, 7, 200, 2):
+            net.step(n)
+    net = snn.Network(spec)
+    run(net)
+    got = everything(net, spec)
+    net.reset()
+    run(net)
+    assert not differing(got, everything(net, spec))
+    net.close()
+    for mode in MODES[:1] if name == "many" else MODES:
+        assert not differing(got, by_modes(snn, spec, mode, run)), mode
+
+
+@pytest.mark.parametrize("name", ["small", "split", "izh"])
+@pytest.mark.parametrize("frac", [0.02, 1.0])
+def test_given_spikes_and_changes_of_path(snn, name, frac):
+    """Spikes set from outside (all at once too: more rows than one listing
+    holds), pending when the path changes, in both directions."""
+    print(f"case: resident spikes {name} {frac}", flush=True)
+    spec = NETS[name]()
+    rng = np.random.default_rng(2)
+    n_pops = len(spec["instances"][0]["pops"])
+    flags = [(rng.random(spec["instances"][0]["pops"][p]["n"]) < frac).astype(np.uint8) for p in range(n_pops)]
+
+    def run(net, change=None):
+        net.step(20)
+        for p in range(n_pops):
+            net.set_last_spikes(0, p, flags[p])
+        if change:
+            net.set_launch(**change)
+        net.step(1)
+        net.step(9)
+    ref = by_modes(snn, spec, dict(mode=0), run)
+    for change in (None, *MODES):
+        net = snn.Network(spec)
+        run(net, change)
+        assert not differing(ref, everything(net, spec)), change
+        net.close()
+
+
+def test_recorded_steps(snn):
+    """Raster ring and voltage sums of resident steps."""
+    print("case: resident records", flush=True)
+    spec = layered(2, 100, 900, 70)
+
+    def run(net):
+        net.step(75)
+        out = [net.vbar_sum(0, 2), net.vbar_sum(1, 2)]
+        for b in range(2):
+            for p in range(3):
+                out += net.raster(b, p, 25, 75)
+        return out
+    got = []
+    for mode in (None, dict(mode=0)):
+        net = snn.Network(spec, record_vbar=("C",), raster_steps=64)
+        if mode:
+            net.set_launch(**mode)
+        got.append(run(net))
+        net.close()
+    assert not differing(*got)
