@@ -407,7 +407,7 @@ hipError_t launch_resident(const ResArgs &a, int feat, int blocks, int block, si
 // Reverse-time adjoint of one population's time-averaged voltage with the
 // spike raster held fixed (snn_adjoint.hip).  Loss neurons are numbered
 // compactly, instance-major: instance b owns [loss_base[b], loss_base[b+1]).
-constexpr int kAdjMaxSub = 8;       // substeps the reverse pass keeps in registers
+constexpr int kAdjMaxSub = 8;       // substeps that the reverse pass supports
 constexpr int kAdjMaxLoss = 1024;   // loss neurons per instance (one block each)
 
 struct AdjArgs {
@@ -423,20 +423,22 @@ struct AdjArgs {
     int64_t n_waves;
     int64_t T;
     int64_t n_pad;               // padded neuron count (stride of the state arrays)
-    const float *ckpt_state;     // checkpoint of this segment: 8 state arrays
-    const int64_t *ckpt_G;       // and the conductance pool
-    const float *next_state;     // checkpoint of the next segment (self-check) or null
-    const int64_t *next_G;
-    uint32_t *mismatch;
-    int64_t t_a;                 // first step of the segment
-    int32_t K;                   // steps in the segment
+    const float *ckpt_state;     // checkpoint of the group's first segment: 8 state arrays,
+    const int64_t *ckpt_G;       // and the conductance pool; the next segments' follow
+    int64_t g_stride;            // conductances per checkpoint
+    uint32_t *mismatch;          // values that differ from the next segment's checkpoint
+    int64_t t_a;                 // first step of the group
+    int32_t K;                   // steps in the group
+    int32_t seg_steps;           // steps in a segment (the recording's last may be shorter)
+    int64_t first_seg, n_seg;    // the group's first segment, segments of the recording
     const int32_t *rp_pool;
     const int32_t *col_pool;
     const float *w_pool;
     const float *gscale;
     double *tape_x;              // [K][4][n_loss]   state at the start of each step
-    double *tape_g;              // [K][n_in_max][n_loss]  delivered conductance (uS)
-    double *lam;                 // [4 + n_in_max][n_loss]  adjoint carried across segments
+    double *tape_g;              // [K][n_in_max][n_loss]  delivered conductance (uS); before the states are
+                                 // recomputed, the delivered increments (int64, 2^-40 uS)
+    double *lam;                 // [4 + n_in_max][n_loss]  adjoint carried across groups
     double *lg;                  // [K][n_in_max][n_loss]   adjoint of the delivered conductance
     const double *dvbar;         // [n_loss]  dL / dVbar
     int32_t substeps;
@@ -447,9 +449,9 @@ struct AdjArgs {
     double *ds;                  // [n_inst] dL / dg_scale
 };
 
-hipError_t launch_adj_recompute(const AdjArgs &a, int block, hipStream_t s);
-hipError_t launch_adj_reverse(const AdjArgs &a, hipStream_t s);
-hipError_t launch_adj_gather(const AdjArgs &a, hipStream_t s);
+// One group of segments; max_inc: the most (inputs x neurons) of an instance's
+// loss population.
+hipError_t launch_adj_group(const AdjArgs &a, int max_inc, hipStream_t s);
 hipError_t launch_gather_vbar(const Seg *segs, const int32_t *loss_seg, const int64_t *loss_base,
                               const int32_t *loss_owner, int64_t n_loss, const double *vsum, double inv_T,
                               double *vbar, hipStream_t s);

@@ -247,7 +247,8 @@ struct snn_net {
     int32_t *d_loss_owner;
     int64_t n_loss;
     int32_t n_in_max;
-    int32_t loss_block;
+    int32_t max_inc;         // most (inputs x neurons) of an instance's loss population
+    int64_t rec_group;       // segments that the net's own tape holds
     int4 *d_gitems;
     int64_t n_gitems;
     double *d_tape_x, *d_tape_g, *d_lg, *d_lam;
@@ -511,6 +512,10 @@ int prepare_graphs(snn_net *net, int64_t n)
 }
 
 int materialize(snn_net *net);
+
+// The backward pass's own tape: at most this much beyond one segment, and
+// steps in a group (a block per step and instance).
+constexpr int64_t kTapeBytes = (int64_t)512 << 20, kTapeSteps = 32768;
 
 constexpr int64_t kResidentMin = 8;        // steps in a call that are worth a cooperative launch
 constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
@@ -2494,7 +2499,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     if (net->substeps > kAdjMaxSub) return fail(SNN_EINVAL, "the adjoint supports at most %d substeps", kAdjMaxSub);
     std::vector<int32_t> lseg(net->n_inst);
     std::vector<int64_t> lbase(net->n_inst + 1, 0);
-    int n_in_max = 1;
+    int n_in_max = 1, max_inc = 1;
     for (int b = 0; b < net->n_inst; ++b) {
         if (pop < 0 || pop >= (int32_t)net->seg_of[b].size()) return fail(SNN_EINVAL, "instance %d has no population %d", b, pop);
         const Seg &S = net->segs[net->seg_of[b][pop]];
@@ -2504,6 +2509,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
         lseg[b] = net->seg_of[b][pop];
         lbase[b + 1] = lbase[b] + S.n;
         n_in_max = std::max(n_in_max, S.n_in);
+        max_inc = std::max(max_inc, S.n_in * S.n);
     }
     const int64_t T = n_steps, K = std::min<int64_t>(ckpt_every, T);
     const int64_t nseg = (T + K - 1) / K;
@@ -2521,36 +2527,43 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
             for (int w = 0; w < nw; ++w) items.push_back(make_int4(b, q, P.pre_seg, w));
         }
     }
-    // (re)allocate the recording
-    void *old[] = {net->d_rec_raster, net->d_ckpt_state, net->d_ckpt_G, net->d_loss_seg, net->d_loss_base,
-                   net->d_loss_owner, net->d_gitems, net->d_tape_x, net->d_tape_g, net->d_lg, net->d_lam};
-    for (void *p : old) dev_free(net, p);
+    // segments per group of the backward pass: as many as kTapeBytes hold, so
+    // that their steps run in parallel
+    const int64_t per_seg = 8 * std::max<int64_t>(n_loss, 1) * K * (4 + 2 * n_in_max);
+    const int64_t group = std::min(nseg, std::max<int64_t>(1, std::min(kTapeBytes / per_seg, kTapeSteps / K)));
+    // (re)allocate the recording, unless the last one had the same shape
+    const bool same = net->d_rec_raster && net->rec_pop == pop && net->rec_T == T && net->rec_K == K;
     net->recorded = false;
-    net->d_rec_raster = (uint64_t *)dev_alloc(net, 8 * (size_t)(T * W));
-    net->d_ckpt_state = (float *)dev_alloc(net, 4 * (size_t)(nseg * 8 * N));
-    net->d_ckpt_G = (int64_t *)dev_alloc(net, 8 * (size_t)(nseg * std::max<int64_t>(net->G_count, 1)));
-    net->d_loss_seg = (int32_t *)dev_alloc(net, 4 * (size_t)net->n_inst);
-    net->d_loss_base = (int64_t *)dev_alloc(net, 8 * (size_t)(net->n_inst + 1));
-    net->d_loss_owner = (int32_t *)dev_alloc(net, 4 * owner.size());
-    net->d_gitems = (int4 *)dev_alloc(net, sizeof(int4) * std::max<size_t>(items.size(), 1));
-    net->d_tape_x = (double *)dev_alloc(net, 8 * (size_t)(K * 4 * std::max<int64_t>(n_loss, 1)));
-    net->d_tape_g = (double *)dev_alloc(net, 8 * (size_t)(K * n_in_max * std::max<int64_t>(n_loss, 1)));
-    net->d_lg = (double *)dev_alloc(net, 8 * (size_t)(K * n_in_max * std::max<int64_t>(n_loss, 1)));
-    net->d_lam = (double *)dev_alloc(net, 8 * (size_t)((4 + n_in_max) * std::max<int64_t>(n_loss, 1)));
-    if (!net->d_rec_raster || !net->d_ckpt_state || !net->d_ckpt_G || !net->d_loss_seg || !net->d_loss_base ||
-        !net->d_loss_owner || !net->d_gitems || !net->d_tape_x || !net->d_tape_g || !net->d_lg || !net->d_lam)
-        return fail(SNN_ENOMEM, "allocation of the adjoint recording failed");
-    if ((rc = h2d(net, net->d_loss_seg, lseg.data(), 4 * lseg.size()))) return rc;
-    if ((rc = h2d(net, net->d_loss_base, lbase.data(), 8 * lbase.size()))) return rc;
-    if ((rc = h2d(net, net->d_loss_owner, owner.data(), 4 * owner.size()))) return rc;
-    if ((rc = h2d(net, net->d_gitems, items.data(), sizeof(int4) * items.size()))) return rc;
+    if (!same) {
+        void *old[] = {net->d_rec_raster, net->d_ckpt_state, net->d_ckpt_G, net->d_loss_seg, net->d_loss_base,
+                       net->d_loss_owner, net->d_gitems, net->d_tape_x, net->d_tape_g, net->d_lg, net->d_lam};
+        for (void *p : old) dev_free(net, p);
+        net->d_rec_raster = nullptr;
+        net->d_ckpt_state = (float *)dev_alloc(net, 4 * (size_t)(nseg * 8 * N));
+        net->d_ckpt_G = (int64_t *)dev_alloc(net, 8 * (size_t)(nseg * std::max<int64_t>(net->G_count, 1)));
+        net->d_loss_seg = (int32_t *)dev_alloc(net, 4 * (size_t)net->n_inst);
+        net->d_loss_base = (int64_t *)dev_alloc(net, 8 * (size_t)(net->n_inst + 1));
+        net->d_loss_owner = (int32_t *)dev_alloc(net, 4 * owner.size());
+        net->d_gitems = (int4 *)dev_alloc(net, sizeof(int4) * std::max<size_t>(items.size(), 1));
+        const size_t steps = (size_t)(group * K), nl = (size_t)std::max<int64_t>(n_loss, 1);
+        net->d_tape_x = (double *)dev_alloc(net, 8 * steps * 4 * nl);
+        net->d_tape_g = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
+        net->d_lg = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
+        net->d_lam = (double *)dev_alloc(net, 8 * (size_t)(4 + n_in_max) * nl);
+        if (!net->d_ckpt_state || !net->d_ckpt_G || !net->d_loss_seg || !net->d_loss_base || !net->d_loss_owner ||
+            !net->d_gitems || !net->d_tape_x || !net->d_tape_g || !net->d_lg || !net->d_lam)
+            return fail(SNN_ENOMEM, "allocation of the adjoint recording failed");
+        if ((rc = h2d(net, net->d_loss_seg, lseg.data(), 4 * lseg.size()))) return rc;
+        if ((rc = h2d(net, net->d_loss_base, lbase.data(), 8 * lbase.size()))) return rc;
+        if ((rc = h2d(net, net->d_loss_owner, owner.data(), 4 * owner.size()))) return rc;
+        if ((rc = h2d(net, net->d_gitems, items.data(), sizeof(int4) * items.size()))) return rc;
+        net->d_rec_raster = (uint64_t *)dev_alloc(net, 8 * (size_t)(T * W));
+        if (!net->d_rec_raster) return fail(SNN_ENOMEM, "allocation of the adjoint recording failed");
+    }
     net->n_loss = n_loss;
     net->n_in_max = n_in_max;
-    // the recompute's block per instance: all of its wavefronts walk a step's
-    // raster words and rows (the step's longest phase), then the first n
-    // threads update the loss neurons; a full block of kAdjMaxLoss threads
-    // spreads that walk over 16 wavefronts instead of the neurons' few
-    net->loss_block = kAdjMaxLoss;
+    net->max_inc = max_inc;
+    net->rec_group = group;
     net->n_gitems = (int64_t)items.size();
     net->rec_pop = pop;
     net->rec_T = T;
@@ -2593,15 +2606,15 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
 
 namespace {
 
-// The backward pass of snn_backward and snn_backward_noalloc: per segment,
-// from the last to the first, recompute the loss population from its
-// checkpoint into the tape, reverse it, gather the weight gradients.  The
-// tape (tape_x, tape_g, lg), the adjoint carried across segments (lam) and
-// the recompute check flag are the callers' scratch; lam, the flag and the
+// The backward pass of snn_backward and snn_backward_noalloc: per group of
+// `group` segments, from the last to the first, recompute the loss population
+// from their checkpoints into the tape, reverse it, gather the weight
+// gradients.  The tape (tape_x, tape_g, lg), the adjoint carried across groups
+// (lam) and the recompute check flag are the callers' scratch; lam, the flag and the
 // two outputs are cleared here, by memset nodes or (fill_kernel) by a fill
 // kernel.
 int run_backward(snn_net *net, const double *dL_dvbar, float *dL_dg, double *dL_dgscale, double *tape_x,
-                 double *tape_g, double *lg, double *lam, uint32_t *flag, bool fill_kernel)
+                 double *tape_g, double *lg, double *lam, uint32_t *flag, int64_t group, bool fill_kernel)
 {
     const int64_t N = net->n_neurons_padded;
     const int64_t gstride = std::max<int64_t>(net->G_count, 1);
@@ -2646,16 +2659,17 @@ int run_backward(snn_net *net, const double *dL_dvbar, float *dL_dg, double *dL_
     a.n_gitems = net->n_gitems;
     a.dg = dL_dg;
     a.ds = dL_dgscale;
-    for (int64_t sg = net->rec_nseg - 1; sg >= 0; --sg) {
+    a.g_stride = gstride;
+    a.seg_steps = net->rec_K;
+    a.n_seg = net->rec_nseg;
+    for (int64_t end = net->rec_nseg; end > 0; end -= group) {
+        const int64_t sg = std::max<int64_t>(end - group, 0);
+        a.first_seg = sg;
         a.t_a = sg * net->rec_K;
-        a.K = (int32_t)std::min<int64_t>(net->rec_K, net->rec_T - a.t_a);
+        a.K = (int32_t)(std::min(end * net->rec_K, net->rec_T) - a.t_a);
         a.ckpt_state = net->d_ckpt_state + sg * 8 * N;
         a.ckpt_G = net->d_ckpt_G + sg * gstride;
-        a.next_state = sg + 1 < net->rec_nseg ? net->d_ckpt_state + (sg + 1) * 8 * N : nullptr;
-        a.next_G = sg + 1 < net->rec_nseg ? net->d_ckpt_G + (sg + 1) * gstride : nullptr;
-        HIP_OK(launch_adj_recompute(a, net->loss_block, net->stream));
-        HIP_OK(launch_adj_reverse(a, net->stream));
-        HIP_OK(launch_adj_gather(a, net->stream));
+        HIP_OK(launch_adj_group(a, net->max_inc, net->stream));
     }
     return SNN_OK;
 }
@@ -2681,7 +2695,7 @@ int snn_backward(snn_net *net, const double *dL_dvbar, float *dL_dg, double *dL_
     if (!net->recorded) return fail(SNN_ESTATE, "call snn_forward_record first");
     if (!dL_dvbar || !dL_dg || !dL_dgscale) return fail(SNN_EINVAL, "NULL argument");
     if ((rc = run_backward(net, dL_dvbar, dL_dg, dL_dgscale, net->d_tape_x, net->d_tape_g, net->d_lg, net->d_lam,
-                           net->d_flag, false)))
+                           net->d_flag, net->rec_group, false)))
         return rc;
     if (mismatch) {
         uint32_t m = 0;
@@ -2705,14 +2719,18 @@ int snn_backward_noalloc(snn_net *net, const double *dL_dvbar, float *dL_dg, dou
                     need, kScratchBytes);
     char *base = static_cast<char *>(scratch_on_device(net->device));
     if (!base) return fail(SNN_EDEVICE, "the scratch array's device address is unknown on device %d", net->device);
-    const size_t nl = (size_t)std::max<int64_t>(net->n_loss, 1), K = (size_t)net->rec_K;
-    const size_t nin = (size_t)net->n_in_max;
+    // as many segments per group as the array holds
+    const size_t nl = (size_t)std::max<int64_t>(net->n_loss, 1), nin = (size_t)net->n_in_max;
+    const size_t per_seg = 8 * nl * (size_t)net->rec_K * (4 + 2 * nin), fixed = 256 + 8 * nl * (4 + nin);
+    const int64_t group = std::min<int64_t>(
+        net->rec_nseg, std::max<int64_t>(1, std::min((int64_t)((kScratchBytes - fixed) / per_seg), kTapeSteps / net->rec_K)));
+    const size_t steps = (size_t)group * (size_t)net->rec_K;
     double *tape_x = reinterpret_cast<double *>(base + 256);
-    double *tape_g = tape_x + K * 4 * nl;
-    double *lg = tape_g + K * nin * nl;
-    double *lam = lg + K * nin * nl;
+    double *tape_g = tape_x + steps * 4 * nl;
+    double *lg = tape_g + steps * nin * nl;
+    double *lam = lg + steps * nin * nl;
     return run_backward(net, dL_dvbar, dL_dg, dL_dgscale, tape_x, tape_g, lg, lam, reinterpret_cast<uint32_t *>(base),
-                        true);
+                        group, true);
 }
 
 }  // extern "C"
