@@ -2188,6 +2188,35 @@ int snn_get_nan_counts(snn_net *net, int32_t *per_instance)
     return d2h(net, per_instance, net->nan_count, 4 * (size_t)net->n_inst);
 }
 
+// Largest weight of every projection in the pool w; *flag: some weight is not
+// finite or is negative.
+static int weight_maxima(snn_net *net, const float *w, std::vector<float> *wmax, uint32_t *flag)
+{
+    const size_t np = net->projs.size();
+    wmax->assign(np, 0.0f);
+    HIP_OK(hipMemsetAsync(net->d_flag, 0, 4, net->stream));
+    HIP_OK(hipMemsetAsync(net->d_wmax, 0, 4 * std::max<size_t>(np, 1), net->stream));
+    HIP_OK(launch_check_weights(w, net->d_projs, (int32_t)np, net->max_nnz, net->d_flag, net->d_wmax, net->stream));
+    HIP_OK(hipMemcpyAsync(flag, net->d_flag, 4, hipMemcpyDeviceToHost, net->stream));
+    if (np) HIP_OK(hipMemcpyAsync(wmax->data(), net->d_wmax, 4 * np, hipMemcpyDeviceToHost, net->stream));
+    HIP_OK(hipStreamSynchronize(net->stream));
+    return SNN_OK;
+}
+
+// Largest sum of a projection's weights onto one post neuron, from the pool w.
+static int largest_column_sum(snn_net *net, const HostProj &H, const float *w_pool, double *out)
+{
+    int rc;
+    std::vector<int32_t> col(H.nnz);
+    std::vector<float> w(H.nnz);
+    if ((rc = d2h(net, col.data(), net->d_col + H.syn_base, 4 * (size_t)H.nnz))) return rc;
+    if ((rc = d2h(net, w.data(), w_pool + H.syn_base, 4 * (size_t)H.nnz))) return rc;
+    std::vector<double> cs(std::max(H.n_post, 1), 0.0);
+    for (int64_t k = 0; k < H.nnz; ++k) cs[col[k]] += w[k];
+    *out = *std::max_element(cs.begin(), cs.end());
+    return SNN_OK;
+}
+
 int snn_set_gscale(snn_net *net, const float *per_instance)
 {
     int rc = check_net(net);
@@ -2196,27 +2225,22 @@ int snn_set_gscale(snn_net *net, const float *per_instance)
     for (int b = 0; b < net->n_inst; ++b)
         if (!(per_instance[b] >= 0.0f) || !std::isfinite(per_instance[b]))
             return fail(SNN_EINVAL, "g_scale of instance %d must be finite and >= 0", b);
-    // same range rule as at create, on the stored weights' column sums
+    // same range rule as at create, on the stored weights: column sums bounded
+    // by longest column * largest weight, added up only where that fails
     std::vector<double> bound(net->projs.size(), 0.0), wbound(net->projs.size(), 0.0);
+    std::vector<float> wmax;
+    uint32_t flag = 0;
+    if ((rc = weight_maxima(net, net->d_w, &wmax, &flag))) return rc;
     for (size_t q = 0; q < net->projs.size(); ++q) {
         const HostProj &H = net->hprojs[q];
-        std::vector<int32_t> col(H.nnz);
-        std::vector<float> w(H.nnz);
-        if ((rc = d2h(net, col.data(), net->d_col + H.syn_base, 4 * (size_t)H.nnz))) return rc;
-        if ((rc = d2h(net, w.data(), net->d_w + H.syn_base, 4 * (size_t)H.nnz))) return rc;
-        std::vector<double> cs(std::max(H.n_post, 1), 0.0);
-        for (int64_t k = 0; k < H.nnz; ++k) cs[col[k]] += w[k];
-        double wm = H.stdp ? (double)net->projs[q].g_max : 0.0;
-        for (int64_t k = 0; k < H.nnz; ++k) wm = std::max(wm, (double)w[k]);
-        wbound[q] = wm;
+        const double g_max = H.stdp ? (double)net->projs[q].g_max : 0.0;
+        wbound[q] = std::max(g_max, (double)wmax[q]);
+        const double s = per_instance[H.inst], floor = g_max * H.n_pre;
+        bound[q] = std::max((double)H.max_col_len * (double)wmax[q], floor) / (1.0 - H.decay);
+        if (bound[q] * s < kGLimit) continue;
         double mx = 0.0;
-        for (double c : cs) mx = std::max(mx, c);
-        if (H.stdp) mx = std::max(mx, (double)net->projs[q].g_max * H.n_pre);
-        const int s = net->seg_of[H.inst][H.post_pop];
-        double decay = 0.0;
-        for (int k = 0; k < net->segs[s].n_in; ++k)
-            if (net->segs[s].in_G[k] == H.G_base) decay = net->segs[s].in_decay[k];
-        bound[q] = mx / (1.0 - decay);
+        if ((rc = largest_column_sum(net, H, net->d_w, &mx))) return rc;
+        bound[q] = std::max(mx, floor) / (1.0 - H.decay);
     }
     if ((rc = check_range(net, bound, wbound, per_instance))) return rc;
     std::copy(per_instance, per_instance + net->n_inst, net->gscale.begin());
@@ -2442,13 +2466,8 @@ int snn_set_weights_device(snn_net *net, const float *src)
     if (!src) return fail(SNN_EINVAL, "src is NULL");
     const size_t np = net->projs.size();
     uint32_t flag = 0;
-    std::vector<uint32_t> wbits(np, 0);
-    HIP_OK(hipMemsetAsync(net->d_flag, 0, 4, net->stream));
-    HIP_OK(hipMemsetAsync(net->d_wmax, 0, 4 * std::max<size_t>(np, 1), net->stream));
-    HIP_OK(launch_check_weights(src, net->d_projs, (int32_t)np, net->max_nnz, net->d_flag, net->d_wmax, net->stream));
-    HIP_OK(hipMemcpyAsync(&flag, net->d_flag, 4, hipMemcpyDeviceToHost, net->stream));
-    if (np) HIP_OK(hipMemcpyAsync(wbits.data(), net->d_wmax, 4 * np, hipMemcpyDeviceToHost, net->stream));
-    HIP_OK(hipStreamSynchronize(net->stream));
+    std::vector<float> wmax;
+    if ((rc = weight_maxima(net, src, &wmax, &flag))) return rc;
     if (flag) return fail(SNN_EINVAL, "weights must be finite and >= 0");
     // the range rules of snn_create: a single increment below kWLimit, and
     // g_scale * column sum / (1 - decay) below kGLimit, checked first on the
@@ -2456,22 +2475,15 @@ int snn_set_weights_device(snn_net *net, const float *src)
     for (size_t q = 0; q < np; ++q) {
         const HostProj &H = net->hprojs[q];
         const Proj &P = net->projs[q];
-        float wmf;
-        std::memcpy(&wmf, &wbits[q], 4);
         const double gs = net->gscale[H.inst];
-        const double wm = std::max(H.stdp ? (double)P.g_max : 0.0, (double)wmf);
+        const double wm = std::max(H.stdp ? (double)P.g_max : 0.0, (double)wmax[q]);
         if (!(wm * gs < kWLimit))
             return fail(SNN_ERANGE, "projection %zu: g_scale * largest weight exceeds %g uS", q, kWLimit);
         double bound = (double)H.max_col_len * wm;
         if (H.stdp) bound = std::max(bound, (double)P.g_max * H.n_pre);
         if (bound * gs / (1.0 - H.decay) < kGLimit) continue;
-        std::vector<int32_t> col(H.nnz);
-        std::vector<float> w(H.nnz);
-        if ((rc = d2h(net, col.data(), net->d_col + H.syn_base, 4 * (size_t)H.nnz))) return rc;
-        if ((rc = d2h(net, w.data(), src + H.syn_base, 4 * (size_t)H.nnz))) return rc;
-        std::vector<double> cs(std::max(H.n_post, 1), 0.0);
-        for (int64_t k = 0; k < H.nnz; ++k) cs[col[k]] += w[k];
-        double mx = *std::max_element(cs.begin(), cs.end());
+        double mx = 0.0;
+        if ((rc = largest_column_sum(net, H, src, &mx))) return rc;
         if (H.stdp) mx = std::max(mx, (double)P.g_max * H.n_pre);
         if (!(mx * gs / (1.0 - H.decay) < kGLimit))
             return fail(SNN_ERANGE, "projection %zu: g_scale * column sum / (1 - decay) exceeds %g uS", q, kGLimit);
