@@ -236,6 +236,11 @@ int64_t snn_time(const snn_net *net);
  * averages (Section 5.1).  Synchronises. */
 int snn_get_spikes(snn_net *net, int32_t inst, int32_t pop, int32_t *counts);
 
+/* The same counts summed over population pop, for every instance (host
+ * int64[n_instances]): avgSpike times the neurons of Fig. 1.  Every instance
+ * must have a population pop.  Synchronises. */
+int snn_get_spike_totals(snn_net *net, int32_t pop, int64_t *totals);
+
 /* Spike raster (the spike times of the discrete-time simulation of
  * Section 2) of population pop of instance inst for steps [t0, t1), which must
  * lie within the last raster_steps steps, or, after snn_forward_record and

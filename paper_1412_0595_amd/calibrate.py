@@ -29,11 +29,11 @@ def sweep_table(net, spec, pop=None):
     """Per-run table of a stepped sweep: nConn, gScale, avgSpike (mean spike
     count per neuron of population pop since create; default: the sweep's
     criterion population, B of the layered model) and NaN count."""
-    n = len(spec["instances"])
     pop = spec.get("pop", 1) if pop is None else pop
     n_conn = np.asarray(spec["n_conn"], np.float64)
     g_scale = np.array([swept_scale(inst) for inst in spec["instances"]], np.float64)
-    avg = np.array([net.spikes(k, pop).mean() for k in range(n)], np.float64)
+    size = np.array([inst["pops"][pop]["n"] for inst in spec["instances"]], np.float64)
+    avg = net.spike_totals(pop) / size
     return n_conn, g_scale, avg, net.nan_counts()
 
 

@@ -254,6 +254,7 @@ struct snn_net {
     double *d_tape_x, *d_tape_g, *d_lg, *d_lam;
     uint32_t *d_flag;
     uint32_t *d_wmax;        // per projection: bits of the largest weight (weight checks)
+    int64_t *d_totals;       // per instance: spikes of a population (snn_get_spike_totals)
     int64_t max_nnz;
 
     ResidentPlan res;
@@ -1430,7 +1431,8 @@ int snn_create(const snn_config *cfg, snn_net **out)
     net->d_wmax = (uint32_t *)dev_alloc(net, 4 * std::max<size_t>(net->projs.size(), 1));
     net->max_nnz = 0;
     for (const HostProj &H : net->hprojs) net->max_nnz = std::max(net->max_nnz, H.nnz);
-    if (!net->d_init_state || !net->d_flag || !net->d_wmax) return bail(fail(SNN_ENOMEM, "device allocation failed"));
+    net->d_totals = (int64_t *)dev_alloc(net, 8 * (size_t)net->n_inst);
+    if (!net->d_init_state || !net->d_flag || !net->d_wmax || !net->d_totals) return bail(fail(SNN_ENOMEM, "device allocation failed"));
     if (hipMemcpy(net->d_init_state, net->vh, 4 * 8 * (size_t)N, hipMemcpyDeviceToDevice) != hipSuccess) {
         (void)hipGetLastError();
         return bail(fail(SNN_EDEVICE, "state copy failed"));
@@ -1495,6 +1497,19 @@ int snn_get_spikes(snn_net *net, int32_t inst, int32_t pop, int32_t *counts)
     if (s < 0) return s;
     if (!counts) return fail(SNN_EINVAL, "counts is NULL");
     return d2h(net, counts, net->counts + net->segs[s].base, 4 * (size_t)net->segs[s].n);
+}
+
+int snn_get_spike_totals(snn_net *net, int32_t pop, int64_t *totals)
+{
+    int rc = check_net(net);
+    if (rc) return rc;
+    if (!totals) return fail(SNN_EINVAL, "totals is NULL");
+    for (int b = 0; b < net->n_inst; ++b) {
+        const int s = seg_index(net, b, pop, false);
+        if (s < 0) return s;
+    }
+    HIP_OK(launch_spike_totals(net->d_segs, (int32_t)net->segs.size(), net->counts, pop, net->d_totals, net->stream));
+    return d2h(net, totals, net->d_totals, 8 * (size_t)net->n_inst);
 }
 
 int snn_get_raster(snn_net *net, int32_t inst, int32_t pop, int64_t t0, int64_t t1, int64_t *offsets, int32_t *ids,

@@ -30,7 +30,7 @@ EXPORTS = [
     "snn_memory_bytes", "snn_get_launch", "snn_set_launch", "snn_time_steps", "snn_time_kernel", "snn_profile_steps",
     "snn_last_error", "snn_reset", "snn_weight_count", "snn_weight_offset", "snn_get_weights_device",
     "snn_set_weights_device", "snn_forward_record", "snn_backward", "snn_gscale_select", "snn_gscale_fit",
-    "snn_backward_noalloc",
+    "snn_backward_noalloc", "snn_get_spike_totals",
 ]
 
 
@@ -109,6 +109,7 @@ def load():
         "snn_get_vbar": (C.c_int, [vp, i32, i32, vp]),
         "snn_get_nan_counts": (C.c_int, [vp, vp]),
         "snn_set_gscale": (C.c_int, [vp, vp]),
+        "snn_get_spike_totals": (C.c_int, [vp, i32, vp]),
         "snn_get_weights": (C.c_int, [vp, i32, i32, vp]),
         "snn_memory_bytes": (C.c_int, [vp, vp]),
         "snn_get_launch": (C.c_int, [vp, vp]),
@@ -373,6 +374,13 @@ class Network:
     def spikes(self, inst, pop):
         out = np.zeros(self._n(inst, pop), np.int32)
         _check(load().snn_get_spikes(self.h, inst, pop, _p(out)))
+        return out
+
+    def spike_totals(self, pop):
+        """Spikes of population pop since create or reset, summed over its
+        neurons, per instance (int64)."""
+        out = np.zeros(self.n_instances, np.int64)
+        _check(load().snn_get_spike_totals(self.h, pop, _p(out)))
         return out
 
     def raster(self, inst, pop, t0, t1):
