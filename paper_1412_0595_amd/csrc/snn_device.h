@@ -247,28 +247,32 @@ __device__ __forceinline__ HHRates hh_rates(double v)
 }
 
 // One forward-Euler substep, every right-hand side from the substep-start
-// state; S holds the population's constants.  The part that the input current
-// does not enter: advances the gates and returns the ionic current (both at
-// the substep's start).  Contractions are written out, so that every kernel
-// rounds alike.
+// state; S holds the population's constants.  In two parts, so that a caller
+// can put the gates' advance (the rates, nearly all of the work) off the path
+// to the voltage: the ionic current and the gates, both at the substep's
+// start.  Contractions are written out, so that every kernel rounds alike.
 template <class P>
-__device__ __forceinline__ double hh_gates(const P &S, double hs, double v, double &m, double &h, double &n)
+__device__ __forceinline__ double hh_ionic(const P &S, double v, double m, double h, double n)
+{
+    const double n2 = n * n;
+    return fma(S.gl, v - S.el, fma(S.gna * (m * m * m * h), v - S.ena, S.gk * (n2 * n2) * (v - S.ek)));
+}
+
+__device__ __forceinline__ void hh_gates(double hs, double v, double &m, double &h, double &n)
 {
     const HHRates r = hh_rates(v);
-    const double n2 = n * n;
-    const double iion = fma(S.gl, v - S.el, fma(S.gna * (m * m * m * h), v - S.ena, S.gk * (n2 * n2) * (v - S.ek)));
     m = fma(hs, fma(1.0 - m, r.am, -(r.bm * m)), m);
     h = fma(hs, fma(1.0 - h, r.ah, -(r.bh * h)), h);
     n = fma(hs, fma(1.0 - n, r.an, -(r.bn * n)), n);
-    return iion;
 }
 
 template <class P>
 __device__ __forceinline__ void hh_substep(const P &S, double hs, double hc, double iin, double &v, double &m,
                                            double &h, double &n)
 {
-    const double iion = hh_gates(S, hs, v, m, h, n);
-    v = fma(hc, iin - iion, v);
+    const double vn = fma(hc, iin - hh_ionic(S, v, m, h, n), v);
+    hh_gates(hs, v, m, h, n);
+    v = vn;
 }
 
 // Whether x stays finite once held in the fp32 state arrays: |x| below

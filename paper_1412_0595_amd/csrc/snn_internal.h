@@ -331,17 +331,27 @@ struct LtpArgs {
 
 // Resident stepping (snn_resident.hip): an instance's words dealt out over
 // the blocks of its cluster.
-constexpr int kResRing = 4;      // steps of spike words in the exchange ring (a power of two)
+constexpr int kResRing = 16;     // steps of spike words in the exchange ring (a power of two)
+constexpr int kResCheck = 8;     // a block that needs no neuron's words reads them every so many steps
+constexpr int kResNeuronRec = 176, kResSourceRec = 32;   // bytes of a word's constants in LDS
 constexpr int kResList = 1024;   // spiking rows a block lists in LDS for one step
 
 // A projection (or the part of it that ends in one block), as the block's
 // source of deliveries.
 struct ResFeed {
-    const int32_t *bounds;   // slice of pre row i: [bounds[i * stride], bounds[i * stride + 1])
-    int32_t stride;
-    int32_t syn;             // the projection's first synapse, from the instance's first
-    int32_t g0;              // LDS conductance index of post neuron 0 (may be negative)
+    const int32_t *bounds;   // slice of pre row i in the block's synapses: [bounds[i], bounds[i + 1])
     int32_t word0;           // first word of the pre population, from the instance's first
+    int32_t n_pre;
+    int32_t lds;             // place of the bounds in the block's LDS, -1: not there
+    int32_t pad_;
+};
+
+struct ResSource {           // the same, to build the block's synapses from
+    int64_t rp_base, syn_base;   // the projection's CSR
+    int64_t bounds0;             // its place in the bounds
+    int32_t n_pre;
+    int32_t c0, c1;              // post neurons [c0, c1)
+    int32_t g0;                  // LDS conductance index of post neuron 0 (may be negative)
 };
 
 struct ResWord {             // 64 neurons of one population
@@ -358,14 +368,12 @@ struct ResBlock {
     int32_t n_state, n_poi;  // words of this block with a membrane (first in its word list) and without
     int32_t n_g, n_feed;     // LDS conductances, feeds
     int64_t word0, feed0;    // this block's entries in the word and feed tables,
-    int64_t wfeed0;          // and in the table of each instance word's feeds
-    int64_t syn_first;       // first synapse of the instance
+    int64_t wfeed0, read0;   // in the table of each instance word's feeds, of the words it reads:
+    int32_t n_early, n_late; // sources' that feed it; all with a membrane
+    int32_t late_feeds;      // 1: some of the latter feed it
+    int32_t pad_;
+    int64_t syn0;            // the block's synapses
     int64_t x_off;           // the instance's exchange ring
-};
-
-struct ResSplit {            // slice bounds to build: one split projection
-    int64_t rp_base, syn_base, out0, start0;
-    int32_t n_pre, parts;
 };
 
 struct ResArgs {
@@ -374,6 +382,8 @@ struct ResArgs {
     const ResWord *words;
     const ResFeed *feeds;
     const uint32_t *wfeeds;  // per block and word of the instance: first feed << 16 | number of feeds
+    const uint32_t *reads;   // per block: words of the instance, early then late
+    const int2 *syn;         // per block and feed, row by row: (LDS conductance, weight)
     uint64_t *xbuf;          // per instance: [kResRing][words][2] of (tag, half word)
     float *vh, *vl, *mh, *ml, *hh, *hl, *nh, *nl;
     int64_t *G;
@@ -386,19 +396,24 @@ struct ResArgs {
     int32_t raster_steps;
     int32_t substeps;
     double hs;
-    const int32_t *col_pool;
-    const float *w_pool;
     const float *gscale;
     const float4 *izp;
     StepState *st;
     int64_t t0, n;
     uint32_t tag0;           // exchange tag of step t0
     int32_t skip_first;      // 1: S(t0 - 1) is already in the conductances
+    int64_t ckpt_every;      // > 0: the state at the start of every step k * ckpt_every < ckpt_end that
+    int64_t ckpt_end;        // a step of the launch ends at goes to checkpoint k
+    float *ckpt_state;       // (8 state arrays)
+    int64_t *ckpt_G;         // and its conductances
+    int64_t g_stride;
     int64_t max_wait;        // wall-clock ticks a block waits for its cluster's words
 };
 
-hipError_t launch_slice_bounds(const ResSplit &d, const int32_t *rp_pool, const int32_t *col_pool,
-                               const int32_t *starts, int32_t *out, hipStream_t s);
+hipError_t launch_resident_bounds(const ResBlock *blocks, int n, const ResSource *srcs, const int32_t *rp_pool,
+                                  const int32_t *col_pool, int32_t *bounds, int32_t *from, int64_t *totals, hipStream_t s);
+hipError_t launch_resident_fill(const ResBlock *blocks, int n, const ResSource *srcs, const int32_t *col_pool,
+                                const float *w_pool, const int32_t *bounds, const int32_t *from, int2 *syn, hipStream_t s);
 // Whether the kernel runs with this block size and LDS, and (together) all
 // blocks are resident at once.
 bool resident_fits(int feat, int block, size_t lds, int blocks, bool together, int n_cu);

@@ -13,11 +13,14 @@
 //
 // A step of a small network is a chain of latencies, not work, and the chain
 // is what this kernel shortens: spike words, a list of the spiking rows in LDS
-// (so that the waves share them evenly), slice bounds, synapses, LDS sums,
-// update.  Deliveries go into two alternating sums, so a wave need not wait
-// for the others' updates before it delivers the next step; and the first
-// Euler substep of the gates and the ionic current do not depend on the step's
-// input, so they run, like the sources' draws, while the words travel.
+// (so that the waves share them evenly), synapses (a block's own, slice after
+// slice; their bounds in LDS where these fit), LDS sums, voltage.  A step's
+// last voltage needs the
+// rates of all substeps but the first, whose gates and ionic current the
+// step's input does not enter, and the last, whose gates only the next step
+// uses: of three substeps' rates one lies before the spike words and two run
+// after they have left, while they travel.  Waves without a neuron draw the
+// sources and poll the words meanwhile.
 #include <algorithm>
 
 #include "snn_device.h"
@@ -27,75 +30,101 @@ namespace snn {
 namespace {
 
 using CResBlock = const __attribute__((address_space(4))) ResBlock;
-using CResWord = const __attribute__((address_space(4))) ResWord;
-using CSeg = const __attribute__((address_space(4))) Seg;
+
+using GlobalI32 = __attribute__((address_space(1))) int32_t;   // (generic loads would wait for LDS and memory alike)
 
 constexpr int kResPoll = 4;    // half words a lane asks for at once
 constexpr int kResState = 5;   // doubles of state per neuron in LDS
+constexpr int kResHelpers = 3; // waves without neurons that take the reading off the others
 
-// The constants of a Traub-Miles population, in scalar registers.
-struct HHConst {
-    double gna, ena, gk, ek, gl, el;
+// A word's constants, in LDS: one round trip where the population record would
+// take several scalar loads in turn.
+struct NeuronRec {
+    double gna, ena, gk, ek, gl, el;      // Traub-Miles
+    double hc, i_ext;                     // dt / substeps / C
+    double erev[kMaxIn], decay[kMaxIn];
+    int32_t g_off[kMaxIn];                // LDS conductances, per incoming projection
+    int32_t n_in, rel, active;            // inputs, word of the instance, lanes with a neuron
+    int32_t izh, rec, izp, inst, seg;     // Izhikevich: place of its parameters
+};
+struct SourceRec {
+    uint32_t seed_lo, seed_hi, pop;
+    int32_t rel, active, j0;              // word of the instance, lanes with a source, its first source
+    uint64_t thresh;
+};
+static_assert(sizeof(NeuronRec) == kResNeuronRec && sizeof(SourceRec) == kResSourceRec, "LDS sizes of the plan");
+
+// A batch of kN slots of up to 64 entries of one slice each: the entries, and
+// which of them the lane adds (bit u: slot u's).  Past the last slice a slot
+// repeats its entries and adds nothing.
+template <int kN>
+struct SlotBatch {
+    int2 e[kN];
+    uint32_t add;
 };
 
-// Poisson draw of step t for lane's neuron j.
-__device__ __forceinline__ bool poisson_spike(CSeg &S, int32_t j, int64_t t)
-{
-    const uint32_t w = philox_first_word((uint32_t)j, (uint32_t)((uint64_t)t & 0xffffffffu),
-                                         (uint32_t)((uint64_t)t >> 32), (uint32_t)S.pop,
-                                         (uint32_t)(S.seed & 0xffffffffu), (uint32_t)(S.seed >> 32));
-    return (uint64_t)w < S.thresh;
-}
+// The next slices of a wave's rows: the one in progress, [k, k1), and the
+// lanes left in rem.
+struct SliceWalk {
+    int32_t b0, b1;      // lane l: its slice's bounds in the block's synapses (empty: none)
+    uint64_t rem;
+    int32_t k, k1;
+};
 
-// One batch of kSlotsN slots of up to 64 entries of one slice each, from the
-// slice in progress [k, k1) and the lanes left in rem; all loads before the
-// atomics.  Past the last slice a slot repeats its entries and adds nothing.
-template <int kSlotsN>
-__device__ __forceinline__ void slots_to_lds(unsigned long long *s_g, const int32_t *col, const float *w, int32_t b0,
-                                             int32_t b1, int32_t go, double s, int lane, uint64_t &rem, int32_t &k,
-                                             int32_t &k1, int32_t &g0)
+template <int kN>
+__device__ __forceinline__ bool load_slots(SlotBatch<kN> &B, SliceWalk &W, const int2 *syn, int lane)
 {
-    int32_t sk[kSlotsN], se[kSlotsN], sg[kSlotsN];
+    if (!W.rem && W.k >= W.k1) return false;
+    B.add = 0;
 #pragma unroll
-    for (int u = 0; u < kSlotsN; ++u) {
-        if (k >= k1 && rem) {
-            const int r = __builtin_ctzll(rem);
-            rem &= rem - 1;
-            k = __builtin_amdgcn_readlane(b0, r);
-            k1 = __builtin_amdgcn_readlane(b1, r);
-            g0 = __builtin_amdgcn_readlane(go, r);
+    for (int u = 0; u < kN; ++u) {
+        if (W.k >= W.k1 && W.rem) {
+            const int r = __builtin_ctzll(W.rem);
+            W.rem &= W.rem - 1;
+            W.k = __builtin_amdgcn_readlane(W.b0, r);
+            W.k1 = __builtin_amdgcn_readlane(W.b1, r);
         }
-        sk[u] = k;
-        se[u] = k1;
-        sg[u] = g0;
-        k += kWave;
+        const int32_t kk = W.k + lane;
+        B.add |= (kk < W.k1 ? 1u : 0u) << u;
+        B.e[u] = syn[(uint32_t)min(kk, W.k1 - 1)];
+        W.k += kWave;
     }
-    int32_t c[kSlotsN];
-    float g[kSlotsN];
-#pragma unroll
-    for (int u = 0; u < kSlotsN; ++u) {
-        const uint32_t kk = (uint32_t)min(sk[u] + lane, se[u] - 1);
-        c[u] = col[kk];
-        g[u] = w[kk];
-    }
-#pragma unroll
-    for (int u = 0; u < kSlotsN; ++u)
-        if (sk[u] + lane < se[u]) atomicAdd(s_g + (sg[u] + c[u]), (unsigned long long)fix_increment(s, g[u]));
+    return true;
 }
 
-// Adds slices into the block's sums: lane l holds its slice's bounds [b0, b1)
-// (relative to the instance's first synapse; empty: none) and the LDS index
-// of the slice's column 0.
-__device__ __forceinline__ void slices_to_lds(unsigned long long *s_g, const int32_t *col, const float *w, int32_t b0,
-                                              int32_t b1, int32_t go, double s, int lane)
+template <int kN>
+__device__ __forceinline__ void add_slots(const SlotBatch<kN> &B, unsigned long long *s_g, double s)
 {
-    uint64_t rem = __ballot(b1 > b0);
-    int32_t k = 0, k1 = 0, g0 = 0;
-    while (rem || k < k1) {
-        if (__popcll(rem) + (k < k1 ? 1 : 0) <= 2 && k1 - k <= kWave)
-            slots_to_lds<2>(s_g, col, w, b0, b1, go, s, lane, rem, k, k1, g0);
-        else
-            slots_to_lds<8>(s_g, col, w, b0, b1, go, s, lane, rem, k, k1, g0);
+    // (the empty asm keeps the wait for this batch ahead of the branches, so
+    // that it does not cover the next batch's loads)
+#pragma unroll
+    for (int u = 0; u < kN; ++u) asm volatile("" ::"v"(B.e[u].x), "v"(B.e[u].y));
+#pragma unroll
+    for (int u = 0; u < kN; ++u)
+        if ((B.add >> u) & 1u)
+            atomicAdd(s_g + B.e[u].x, (unsigned long long)fix_increment(s, __int_as_float(B.e[u].y)));
+}
+
+// Adds slices into the block's conductances; a batch's loads are in flight
+// while the one before is added.
+__device__ __forceinline__ void slices_to_lds(unsigned long long *s_g, const int2 *syn, int32_t b0, int32_t b1, double s,
+                                              int lane)
+{
+    SliceWalk W{b0, b1, __ballot(b1 > b0), 0, 0};
+    if (__popcll(W.rem) <= 2 && !__any(b1 - b0 > kWave)) {
+        SlotBatch<2> A;
+        if (load_slots(A, W, syn, lane)) add_slots(A, s_g, s);
+        return;
+    }
+    SlotBatch<8> A, B;
+    if (!load_slots(A, W, syn, lane)) return;
+    for (;;) {
+        const bool more_b = load_slots(B, W, syn, lane);
+        add_slots(A, s_g, s);
+        if (!more_b) return;
+        const bool more_a = load_slots(A, W, syn, lane);
+        add_slots(B, s_g, s);
+        if (!more_a) return;
     }
 }
 
@@ -106,7 +135,7 @@ template <int FEAT>
 __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
 {
     extern __shared__ __align__(16) char s_mem[];
-    __shared__ uint32_t s_fail, s_cnt[3];   // rows listed per step, of three in turn
+    __shared__ uint32_t s_fail, s_cnt[2], s_src[2];   // rows listed, source words taken; of alternating steps
     const int lane = threadIdx.x & (kWave - 1);
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nt = (int)blockDim.x, nw = nt >> 6;
@@ -114,37 +143,78 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
 
     CResBlock &B = ((CResBlock *)a.blocks)[blockIdx.x];
     const int n_state = B.n_state, n_poi = B.n_poi, n_words = B.n_words, n_g = B.n_g;
+    const int n_early = B.n_early, n_read = n_early + B.n_late;
     const int64_t w_first = B.w_first;      // the instance's first spike word
     const bool multi = B.n_blocks > 1;
-    CResWord *words = (CResWord *)a.words + B.word0;
+    const bool late_feeds = B.late_feeds != 0;
     const double s_fix = (double)a.gscale[B.inst] * kFixOne;
-    const int32_t *col = a.col_pool + B.syn_first;
-    const float *wt = a.w_pool + B.syn_first;
+    const int2 *syn = a.syn + B.syn0;
     uint64_t *xw = a.xbuf + B.x_off;        // kResRing slots of 2 n_words tagged halves
 
-    // LDS: conductances, the deliveries of two alternating steps, neuron
-    // state, recorded sums, feeds, spike words of two steps, each word's feeds,
-    // the rows (neuron of the instance) listed for three steps in turn
+    // LDS: conductances, neuron state, recorded sums, feeds, the words'
+    // constants, spike words of two steps, the words that the block reads
+    // (sources' first), each word's feeds, the listed rows (neurons of the
+    // instance), slice bounds of the feeds that have them here
     unsigned long long *s_g = reinterpret_cast<unsigned long long *>(s_mem);
-    unsigned long long *s_acc = s_g + n_g;
-    double *s_state = reinterpret_cast<double *>(s_acc + 2 * n_g);
+    double *s_state = reinterpret_cast<double *>(s_g + n_g);
     double *s_vsum = s_state + n_state * kResState * kWave;
     ResFeed *s_feed = reinterpret_cast<ResFeed *>(s_vsum + (kRec ? n_state * kWave : 0));
-    uint64_t *s_word = reinterpret_cast<uint64_t *>(s_feed + B.n_feed);
-    uint32_t *s_wfeed = reinterpret_cast<uint32_t *>(s_word + 2 * n_words);
+    NeuronRec *s_rec = reinterpret_cast<NeuronRec *>(s_feed + B.n_feed);
+    SourceRec *s_src_rec = reinterpret_cast<SourceRec *>(s_rec + n_state);
+    uint64_t *s_word = reinterpret_cast<uint64_t *>(s_src_rec + n_poi);
+    uint32_t *s_read = reinterpret_cast<uint32_t *>(s_word + 2 * n_words);
+    uint32_t *s_wfeed = s_read + n_read;
     uint32_t *s_list = s_wfeed + n_words;
+    int32_t *s_bounds = reinterpret_cast<int32_t *>(s_list + kResList);
 
     const int64_t t0 = a.t0, t_end = a.t0 + a.n;
-    if (threadIdx.x == 0) s_fail = s_cnt[0] = s_cnt[1] = s_cnt[2] = 0;
-    for (int i = threadIdx.x; i < 2 * n_g; i += nt) s_acc[i] = 0;
+    if (threadIdx.x == 0) s_fail = s_cnt[0] = s_cnt[1] = s_src[0] = s_src[1] = 0;
     for (int i = threadIdx.x; i < B.n_feed; i += nt) s_feed[i] = a.feeds[B.feed0 + i];
     for (int i = threadIdx.x; i < n_words; i += nt) s_wfeed[i] = a.wfeeds[B.wfeed0 + i];
+    for (int i = threadIdx.x; i < n_read; i += nt) s_read[i] = a.reads[B.read0 + i];
+    for (int w = threadIdx.x; w < n_state + n_poi; w += nt) {
+        const ResWord &W = a.words[B.word0 + w];
+        const Seg &S = a.segs[W.seg];
+        const int32_t rel = (int32_t)(W.gw - w_first), j0 = (int32_t)(W.gw * kWave - S.base);
+        const int32_t active = min(S.n - j0, kWave);
+        if (w < n_state) {
+            NeuronRec &R = s_rec[w];
+            R.gna = S.gna;
+            R.ena = S.ena;
+            R.gk = S.gk;
+            R.ek = S.ek;
+            R.gl = S.gl;
+            R.el = S.el;
+            R.hc = a.hs * S.inv_c;
+            R.i_ext = S.i_ext;
+            for (int q = 0; q < kMaxIn; ++q) {
+                R.erev[q] = q < S.n_in ? S.in_erev[q] : 0.0;
+                R.decay[q] = q < S.n_in ? S.in_decay[q] : 0.0;
+                R.g_off[q] = q < S.n_in ? W.g_off[q] : 0;
+            }
+            R.n_in = S.n_in;
+            R.rel = rel;
+            R.active = active;
+            R.izh = S.kind == kIzh;
+            R.rec = S.record_vbar;
+            R.izp = (int32_t)S.izp_base + j0;
+            R.inst = S.inst;
+            R.seg = W.seg;
+        } else {
+            s_src_rec[w - n_state] = SourceRec{(uint32_t)S.seed, (uint32_t)(S.seed >> 32), (uint32_t)S.pop, rel, active, j0,
+                                               S.thresh};
+        }
+    }
+    for (int f = 0; f < B.n_feed; ++f) {
+        const ResFeed F = a.feeds[B.feed0 + f];
+        if (F.lds >= 0)
+            for (int i = threadIdx.x; i <= F.n_pre; i += nt) s_bounds[F.lds + i] = F.bounds[i];
+    }
     __syncthreads();
 
-    // A word of step t: to the cluster (a single block: to its own list l) and
-    // the records.
-    auto publish = [&](int64_t t, int l, int64_t gw, uint64_t ball) {
-        const int rel = (int)(gw - w_first);
+    // A word of step t: to the cluster (a single block: to its own words and,
+    // with a membrane, list) and the records.
+    auto publish = [&](int64_t t, bool list, int rel, uint64_t ball) __attribute__((always_inline)) {
         if (multi) {
             if (lane < 2) {
                 const uint64_t tag = (uint64_t)(uint32_t)(a.tag0 + (uint32_t)(t - t0)) << 32;
@@ -153,232 +223,308 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
             }
         } else {
             if (lane == 0) s_word[(t & 1) * n_words + rel] = ball;
-            if (ball != 0 && s_wfeed[rel] != 0) {
+            if (list && ball != 0 && s_wfeed[rel] != 0) {
                 uint32_t at = 0;
-                if (lane == 0) at = atomicAdd(&s_cnt[l], (uint32_t)__popcll(ball));
+                if (lane == 0) at = atomicAdd(&s_cnt[t & 1], (uint32_t)__popcll(ball));
                 at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull));
-                if (((ball >> lane) & 1ull) && at < (uint32_t)kResList) s_list[l * kResList + at] = rel * kWave + lane;
+                if (((ball >> lane) & 1ull) && at < (uint32_t)kResList) s_list[at] = rel * kWave + lane;
             }
         }
         if (lane == 0) {
-            if (a.raster) a.raster[(t % a.raster_steps) * a.n_waves + gw] = ball;
-            if (t == t_end - 1) a.bits[(t & 1) * a.n_waves + gw] = ball;
+            if (a.raster) a.raster[(t % a.raster_steps) * a.n_waves + w_first + rel] = ball;
+            if (t == t_end - 1) a.bits[(t & 1) * a.n_waves + w_first + rel] = ball;
         }
     };
-    // The block's Poisson words of step t (the last waves first: the first
-    // ones have the longer share of the neurons).
-    auto sources = [&](int64_t t, int l) {
-        for (int w = nw - 1 - wid; w < n_poi; w += nw) {
-            CResWord &W = words[n_state + w];
-            CSeg &S = ((CSeg *)a.segs)[W.seg];
-            const int64_t gid = W.gw * kWave + lane;
-            const int32_t j = (int32_t)(gid - S.base);
-            const bool spike = j < S.n && poisson_spike(S, j, t);
-            publish(t, l, W.gw, __ballot(spike));
-            if (spike) atomicAdd(&a.counts[gid], 1);
+    // The block's Poisson words of step t, two at a time by the next free wave
+    // (one draw's dependent products hide behind the other's).
+    auto sources = [&](int64_t t) __attribute__((always_inline)) {
+        while (n_poi > 0) {
+            int w = 0;
+            if (lane == 0) w = (int)atomicAdd(&s_src[t & 1], 2u);
+            w = __builtin_amdgcn_readfirstlane(w);
+            if (w >= n_poi) break;
+            const int w2 = min(w + 1, n_poi - 1);
+            auto draw = [&](const SourceRec &R) __attribute__((always_inline)) {
+                return philox_first_word((uint32_t)(R.j0 + lane), (uint32_t)t, (uint32_t)((uint64_t)t >> 32), R.pop,
+                                         R.seed_lo, R.seed_hi);
+            };
+            auto finish = [&](const SourceRec &R, uint32_t x) __attribute__((always_inline)) {
+                const int rel = __builtin_amdgcn_readfirstlane(R.rel);
+                const bool spike = lane < R.active && (uint64_t)x < R.thresh;
+                publish(t, false, rel, __ballot(spike));
+                if (spike) atomicAdd(&a.counts[(w_first + rel) * kWave + lane], 1);
+            };
+            const uint32_t x = draw(s_src_rec[w]), x2 = draw(s_src_rec[w2]);
+            finish(s_src_rec[w], x);
+            if (w2 > w) finish(s_src_rec[w2], x2);
         }
+    };
+    // Half words [i0, i0 + 64 kResPoll) of step t among those that the block
+    // reads, up to `end`; waits for them.
+    auto read_halves = [&](int64_t t, int i0, int end, uint32_t (&half)[kResPoll]) __attribute__((always_inline)) {
+        if (t < t0) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(a.bits + (t & 1) * a.n_waves + w_first);
+#pragma unroll
+            for (int u = 0; u < kResPoll; ++u) {
+                const int i = i0 + u * kWave + lane;
+                half[u] = i < end && !a.skip_first ? src[2 * s_read[i >> 1] + (i & 1)] : 0u;
+            }
+            asm volatile("");
+            return;
+        }
+        if (!multi) {
+            const uint32_t *src = reinterpret_cast<const uint32_t *>(s_word + (t & 1) * n_words);
+#pragma unroll
+            for (int u = 0; u < kResPoll; ++u) {
+                const int i = i0 + u * kWave + lane;
+                half[u] = i < end ? src[2 * s_read[i >> 1] + (i & 1)] : 0u;
+            }
+            return;
+        }
+        // A ring slot is written again kResRing steps later: its writer has
+        // then seen a later step's words of every block that reads it, each
+        // published after that block had read the slot.  (A block of sources
+        // that nothing reads may fall further behind and find later tags;
+        // it has no use for the words.)
+        const uint32_t tag = a.tag0 + (uint32_t)(t - t0);
+        const uint64_t *src = xw + (t & (kResRing - 1)) * 2 * n_words;
+        const int64_t since = wall_clock64();
+        uint32_t at[kResPoll];
+#pragma unroll
+        for (int u = 0; u < kResPoll; ++u) {
+            const int i = min(i0 + u * kWave + lane, end - 1);
+            at[u] = 2 * s_read[i >> 1] + (i & 1);
+        }
+        for (uint32_t tries = 1;; ++tries) {
+            uint64_t x[kResPoll];
+#pragma unroll
+            for (int u = 0; u < kResPoll; ++u)
+                if (i0 + u * kWave < end) x[u] = __hip_atomic_load(src + at[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bool here = true;
+#pragma unroll
+            for (int u = 0; u < kResPoll; ++u) {
+                half[u] = 0u;
+                if (i0 + u * kWave < end) {
+                    here &= (int32_t)((uint32_t)(x[u] >> 32) - tag) >= 0;
+                    if (i0 + u * kWave + lane < end) half[u] = (uint32_t)x[u];
+                }
+            }
+            if (__all(here)) break;
+            // the blocks are resident together (cooperative launch), so a
+            // wait this long is a fault: flag it and end
+            if ((tries & 1023u) == 0 && wall_clock64() - since > a.max_wait) {
+                s_fail = 1;
+#pragma unroll
+                for (int u = 0; u < kResPoll; ++u) half[u] = 0u;
+                break;
+            }
+        }
+    };
+    // Adds the slices of the rows that its lanes hold (neurons of the
+    // instance; -1: none).
+    auto deliver_rows = [&](int32_t row) __attribute__((always_inline)) {
+        const uint32_t e = row >= 0 ? s_wfeed[row >> 6] : 0u;      // first feed, number of feeds
+        const uint32_t f0 = e >> 16, nf = e & 0xffffu;
+        for (uint32_t r = 0; __any(r < nf); ++r) {
+            int32_t b0 = 0, b1 = 0;
+            if (r < nf) {
+                const ResFeed F = s_feed[f0 + r];
+                const int32_t i = row - F.word0 * kWave;
+                if (F.lds >= 0) {
+                    b0 = s_bounds[F.lds + i];
+                    b1 = s_bounds[F.lds + i + 1];
+                } else {
+                    const GlobalI32 *bd = (const GlobalI32 *)F.bounds + i;
+                    b0 = bd[0];
+                    b1 = bd[1];
+                }
+            }
+            slices_to_lds(s_g, syn, b0, b1, s_fix, lane);
+        }
+    };
+    // Lists the rows of half words [begin, end) of step t.
+    auto list_rows = [&](int64_t t, int begin, int end) __attribute__((always_inline)) {
+        for (int i0 = begin; i0 < end; i0 += kResPoll * kWave) {
+            uint32_t half[kResPoll];
+            read_halves(t, i0, end, half);
+#pragma unroll
+            for (int u = 0; u < kResPoll; ++u) {
+                const int i = i0 + u * kWave + lane;
+                if (i >= end) continue;
+                const uint32_t rel = s_read[i >> 1];
+                uint32_t h = half[u];
+                reinterpret_cast<uint32_t *>(s_word + (t & 1) * n_words)[2 * rel + (i & 1)] = h;
+                if (h != 0 && s_wfeed[rel] != 0) {
+                    uint32_t at = atomicAdd(&s_cnt[t & 1], (uint32_t)__popc(h));
+                    for (; h != 0 && at < (uint32_t)kResList; h &= h - 1, ++at)
+                        s_list[at] = rel * kWave + (i & 1) * 32 + __builtin_ctz(h);
+                }
+            }
+        }
+    };
+    // Delivers the listed rows of step t, dealt out over the waves; if there
+    // were more than the list holds, those of the half words that the block
+    // read.
+    auto deliver_list = [&](int64_t t) __attribute__((always_inline)) {
+        const int n_rows = (int)s_cnt[t & 1];
+        if (threadIdx.x == 0) s_cnt[(t + 1) & 1] = s_src[t & 1] = 0;   // (t + 1's sources are drawn)
+        if (n_rows <= kResList) {
+            for (int base = 0; base < n_rows; base += nt) {
+                const int i = base + lane * nw + wid;
+                deliver_rows(i < n_rows ? (int32_t)s_list[i] : -1);
+            }
+            return;
+        }
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(s_word + (t & 1) * n_words);
+        for (int base = 0; base < 2 * n_read; base += nt) {
+            const int i = base + lane * nw + wid;
+            const uint32_t at = i < 2 * n_read ? 2 * s_read[i >> 1] + (i & 1) : 0u;
+            uint32_t h = i < 2 * n_read && s_wfeed[at >> 1] != 0 ? w[at] : 0u;
+            for (; __any(h != 0); h &= h - 1) deliver_rows(h != 0 ? at * 32 + __builtin_ctz(h) : -1);
+        }
+    };
+    // a wave's share of half words [begin, end), as wave h of nh
+    auto share = [&](int &begin, int &end, int h, int nh) __attribute__((always_inline)) {
+        const int each = (end - begin + nh - 1) / nh, first = begin + h * each;
+        end = min(first + each, end);
+        begin = first;
     };
     // Traub-Miles: the part of a step's first substep that its input does not
     // enter, from (v, m, h, n) to LDS: v, the gates after it, the ionic current.
-    auto hh_ahead = [&](CSeg &S, double *x, double v, double m, double h, double n) {
-        const HHConst P{S.gna, S.ena, S.gk, S.ek, S.gl, S.el};
+    auto hh_ahead = [&](const NeuronRec &P, double *x, double v, double m, double h, double n) __attribute__((always_inline)) {
         x[0] = v;
-        x[4 * kWave] = hh_gates(P, a.hs, v, m, h, n);
+        x[4 * kWave] = hh_ionic(P, v, m, h, n);
+        hh_gates(a.hs, v, m, h, n);
         x[kWave] = m;
         x[2 * kWave] = h;
         x[3 * kWave] = n;
     };
 
-    // ---- state in, the sources' first step
+    // ---- state in
     for (int w = wid; w < n_state; w += nw) {
-        CResWord &W = words[w];
-        CSeg &S = ((CSeg *)a.segs)[W.seg];
-        const int64_t gid = W.gw * kWave + lane;
+        const NeuronRec &R = s_rec[w];
+        const Seg &S = a.segs[R.seg];
+        const int64_t gid = (w_first + R.rel) * kWave + lane;
         const int32_t jj = min((int32_t)(gid - S.base), S.n - 1);
         double *x = s_state + w * kResState * kWave + lane;
 #pragma unroll
         for (int q = 0; q < kMaxIn; ++q)
-            if (q < S.n_in) s_g[W.g_off[q] + lane] = (unsigned long long)a.G[S.in_G[q] + jj];
-        if constexpr (kRec) s_vsum[w * kWave + lane] = S.record_vbar ? a.vsum[gid] : 0.0;
+            if (q < S.n_in) s_g[R.g_off[q] + lane] = (unsigned long long)a.G[S.in_G[q] + jj];
+        if constexpr (kRec) s_vsum[w * kWave + lane] = R.rec ? a.vsum[gid] : 0.0;
         const double v = pair_load(a.vh, a.vl, gid), m = pair_load(a.mh, a.ml, gid);
-        if (!kIzhOn || S.kind == kHH) {
-            hh_ahead(S, x, v, m, pair_load(a.hh, a.hl, gid), pair_load(a.nh, a.nl, gid));
+        if (!kIzhOn || !R.izh) {
+            hh_ahead(R, x, v, m, pair_load(a.hh, a.hl, gid), pair_load(a.nh, a.nl, gid));
         } else {
             x[0] = v;
             x[kWave] = m;
         }
     }
-    int l_prev = 0, l_cur = 1, l_next = 2;   // lists of S(t - 1), S(t), S(t + 1)
-    sources(t0, l_cur);
-
-    const int h_share = (2 * n_words + nw - 1) / nw;
-    const int h_begin = wid * h_share, h_end = min(h_begin + h_share, 2 * n_words);
-    // Adds the slices of the rows that its lanes hold (neurons of the
-    // instance; -1: none).
-    auto deliver_rows = [&](unsigned long long *acc, int32_t row) {
-        const uint32_t e = row >= 0 ? s_wfeed[row >> 6] : 0u;      // first feed, number of feeds
-        const uint32_t f0 = e >> 16, nf = e & 0xffffu;
-        for (uint32_t r = 0; __any(r < nf); ++r) {
-            int32_t b0 = 0, b1 = 0, go = 0;
-            if (r < nf) {
-                const ResFeed F = s_feed[f0 + r];
-                const int64_t at = (int64_t)(row - F.word0 * kWave) * F.stride;
-                b0 = F.bounds[at] + F.syn;
-                b1 = F.bounds[at + 1] + F.syn;
-                go = F.g0;
-            }
-            slices_to_lds(acc, col, wt, b0, b1, go, s_fix, lane);
-        }
-    };
-
-    for (int64_t t = t0; t < t_end; ++t) {
-        // ---- the rows of S(t - 1): a lane per half word, each wave an equal
-        // share of them (a single block has listed them as it published)
-        uint32_t *pw = reinterpret_cast<uint32_t *>(s_word + ((t + 1) & 1) * n_words);
-        if (multi || t == t0) {
-            for (int i0 = h_begin; i0 < h_end; i0 += kResPoll * kWave) {
-                uint32_t half[kResPoll];
-                if (t == t0) {
-                    const uint32_t *src = reinterpret_cast<const uint32_t *>(a.bits + ((t + 1) & 1) * a.n_waves + w_first);
-#pragma unroll
-                    for (int u = 0; u < kResPoll; ++u) {
-                        const int i = i0 + u * kWave + lane;
-                        half[u] = i < h_end && !a.skip_first ? src[i] : 0u;
-                    }
-                } else {
-                    // A ring slot is written again kResRing steps later: its
-                    // writer has then seen a later step's words of every block,
-                    // each published after its block had read the slot.
-                    const uint32_t tag = a.tag0 + (uint32_t)(t - 1 - t0);
-                    const uint64_t *src = xw + ((t - 1) & (kResRing - 1)) * 2 * n_words;
-                    const int64_t since = wall_clock64();
-                    for (uint32_t tries = 1;; ++tries) {
-                        uint64_t x[kResPoll];
-#pragma unroll
-                        for (int u = 0; u < kResPoll; ++u)
-                            if (i0 + u * kWave < h_end)
-                                x[u] = __hip_atomic_load(src + min(i0 + u * kWave + lane, h_end - 1), __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                        bool here = true;
-#pragma unroll
-                        for (int u = 0; u < kResPoll; ++u) {
-                            half[u] = 0u;
-                            if (i0 + u * kWave < h_end) {
-                                here &= (uint32_t)(x[u] >> 32) == tag;
-                                if (i0 + u * kWave + lane < h_end) half[u] = (uint32_t)x[u];
-                            }
-                        }
-                        if (__all(here)) break;
-                        // the blocks are resident together (cooperative launch),
-                        // so a wait this long is a fault: flag it and end
-                        if ((tries & 1023u) == 0 && wall_clock64() - since > a.max_wait) {
-                            s_fail = 1;
-#pragma unroll
-                            for (int u = 0; u < kResPoll; ++u) half[u] = 0u;
-                            break;
-                        }
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kResPoll; ++u) {
-                    const int i = i0 + u * kWave + lane;
-                    uint32_t h = half[u];
-                    if (i < h_end) pw[i] = h;
-                    if (h != 0 && s_wfeed[i >> 1] != 0) {
-                        uint32_t at = atomicAdd(&s_cnt[l_prev], (uint32_t)__popc(h));
-                        for (; h != 0 && at < (uint32_t)kResList; h &= h - 1, ++at)
-                            s_list[l_prev * kResList + at] = i * 32 + __builtin_ctz(h);
-                    }
-                }
-            }
-        }
-        __syncthreads();
-
-        // ---- deliver them: a row per lane, dealt out over the waves
-        unsigned long long *acc = s_acc + (t & 1) * n_g;
-        const int n_rows = (int)s_cnt[l_prev];
-        if (threadIdx.x == 0) s_cnt[l_next] = 0;
-        if (n_rows <= kResList) {
-            for (int base = 0; base < n_rows; base += nt) {
-                const int i = base + lane * nw + wid;
-                deliver_rows(acc, i < n_rows ? (int32_t)s_list[l_prev * kResList + i] : -1);
-            }
-        } else {
-            // more rows than the list holds: from the words, row by row of a
-            // lane's half word
-            for (int i0 = h_begin; i0 < h_end; i0 += kWave) {
-                const int i = i0 + lane;
-                uint32_t h = i < h_end ? pw[i] : 0u;
-                for (; __any(h != 0); h &= h - 1) deliver_rows(acc, h != 0 ? i * 32 + __builtin_ctz(h) : -1);
-            }
-        }
-        __syncthreads();
-        if (multi && s_fail) {
-            if (threadIdx.x == 0) atomicOr(&a.st->overflow, 4u);
-            return;
-        }
-
-        // ---- update the block's neurons, one word per wave at a time
-        for (int w = wid; w < n_state; w += nw) {
-            CResWord &W = words[w];
-            CSeg &S = ((CSeg *)a.segs)[W.seg];
-            const int64_t gid = W.gw * kWave + lane;
-            const int32_t j = (int32_t)(gid - S.base), n_in = S.n_in;
-            const bool active = j < S.n;
+    // The waves without a word to update (at least kResHelpers of them; else
+    // all, after their updates) read the words; those beside a block of
+    // neurons that only sources feed are read every kResCheck steps, which
+    // keeps the cluster's blocks within the ring.
+    const int n_upd = min(n_state, nw);
+    const bool helpers = nw - n_upd >= kResHelpers;
+    const int help_i = helpers ? wid - n_upd : wid, help_n = helpers ? nw - n_upd : nw;
+    int e_begin = 0, e_end = 2 * n_early, r_begin = 0, r_end = 2 * n_read;
+    share(e_begin, e_end, help_i, help_n);
+    share(r_begin, r_end, help_i, help_n);
+    // the next step whose starting state is also left as a checkpoint
+    int64_t next_ckpt = a.ckpt_every > 0 ? (t0 / a.ckpt_every + 1) * a.ckpt_every : -1;
+    // (step t0 - 1 has only the part that follows its update)
+    for (int64_t t = t0 - 1;; ++t) {
+        // ---- the block's neurons up to the voltage after the step, one word
+        // per wave at a time
+        for (int w = t < t0 ? n_state : wid; w < n_state; w += nw) {
+            const NeuronRec &R = s_rec[w];
+            const int n_in = __builtin_amdgcn_readfirstlane(R.n_in), rel = __builtin_amdgcn_readfirstlane(R.rel);
+            const bool active = lane < R.active;
             double *x = s_state + w * kResState * kWave + lane;
-            double v = x[0];
-            const double v0 = v;
-            double iin = S.i_ext;
-#pragma unroll
-            for (int q = 0; q < kMaxIn; ++q)
-                if (q < n_in) {
-                    const int32_t at = W.g_off[q] + lane;
-                    const int64_t g = (int64_t)(s_g[at] + acc[at]);
-                    acc[at] = 0;
-                    iin += (double)g * kFixInv * (S.in_erev[q] - v0);
-                    s_g[at] = (unsigned long long)fix_decay(g, S.in_decay[q]);
-                }
+            double v = x[0], m = x[kWave];              // (Izhikevich: m is u)
+            double h = x[2 * kWave], n = x[3 * kWave];
+            const double iion = x[4 * kWave], v0 = v;
+            double iin = R.i_ext;
+            auto input = [&](int q) __attribute__((always_inline)) {
+                const int32_t at = R.g_off[q] + lane;
+                const int64_t g = (int64_t)s_g[at];
+                iin += (double)g * kFixInv * (R.erev[q] - v0);
+                s_g[at] = (unsigned long long)fix_decay(g, R.decay[q]);
+            };
+            if (n_in > 0) input(0);
+            if (n_in > 1) input(1);
+            if (n_in > 2) input(2);
+            if (n_in > 3) input(3);
             bool spike;
-            double m = x[kWave], h = 0.0, n = 0.0;      // (Izhikevich: m is u)
-            const bool is_hh = !kIzhOn || S.kind == kHH;
-            if (is_hh) {
-                h = x[2 * kWave];
-                n = x[3 * kWave];
-                const HHConst P{S.gna, S.ena, S.gk, S.ek, S.gl, S.el};
-                const double hc = a.hs * S.inv_c;
-                v = fma(hc, iin - x[4 * kWave], v);     // the first substep, begun by hh_ahead
-                for (int k = 1; k < a.substeps; ++k) hh_substep(P, a.hs, hc, iin, v, m, h, n);
+            if (!kIzhOn || !__builtin_amdgcn_readfirstlane(R.izh)) {
+                v = fma(R.hc, iin - iion, v);           // the first substep, begun by hh_ahead
+                for (int k = 2; k < a.substeps; ++k) hh_substep(R, a.hs, R.hc, iin, v, m, h, n);
+                const double vl = v;
+                if (a.substeps > 1) v = fma(R.hc, iin - hh_ionic(R, v, m, h, n), v);
                 spike = active && (v0 < 0.0) && (v >= 0.0);
+                publish(t, true, rel, __ballot(spike));
+                // the last substep's gates follow from its starting voltage vl
+                x[2 * kWave] = h;
+                x[3 * kWave] = n;
+                x[4 * kWave] = vl;
+                if (active && fits_fp32(v0) && !fits_fp32(v)) atomicAdd(&a.nan_count[R.inst], 1);
             } else {
-                const float4 pr = a.izp[S.izp_base + min(j, S.n - 1)];
+                const float4 pr = a.izp[R.izp + min(lane, R.active - 1)];
                 for (int k = 0; k < a.substeps; ++k) izh_substep((double)pr.x, (double)pr.y, a.hs, iin, v, m);
                 spike = active && v >= kIzhPeak;
-                if (active && fits_fp32(v0) && !fits_fp32(v)) atomicAdd(&a.nan_count[S.inst], 1);
+                publish(t, true, rel, __ballot(spike));
+                if (active && fits_fp32(v0) && !fits_fp32(v)) atomicAdd(&a.nan_count[R.inst], 1);
                 if (spike) {
                     v = (double)pr.z;
                     m = m + (double)pr.w;
                 }
             }
-            publish(t, l_cur, W.gw, __ballot(spike));
-            if (is_hh && active && fits_fp32(v0) && !fits_fp32(v)) atomicAdd(&a.nan_count[S.inst], 1);
-            if (spike) atomicAdd(&a.counts[gid], 1);
-            if (kRec && S.record_vbar) s_vsum[w * kWave + lane] += v;
+            x[0] = v;
+            x[kWave] = m;
+            if (spike) atomicAdd(&a.counts[(w_first + rel) * kWave + lane], 1);
+        }
+        // ---- the rest of their step and the start of the next
+        for (int w = t < t0 ? n_state : wid; w < n_state; w += nw) {
+            const NeuronRec &R = s_rec[w];
+            double *x = s_state + w * kResState * kWave + lane;
+            double v = x[0], m = x[kWave], h = 0.0, n = 0.0;
+            const bool is_hh = !kIzhOn || !__builtin_amdgcn_readfirstlane(R.izh);
+            if (is_hh) {
+                h = x[2 * kWave];
+                n = x[3 * kWave];
+                if (a.substeps > 1) hh_gates(a.hs, x[4 * kWave], m, h, n);
+            }
+            if (kRec && R.rec) s_vsum[w * kWave + lane] += v;
             // the state is held as fp32 pairs between steps
             float vh, vl, mh, ml, hh, hl, nh, nl;
             pair_split(v, vh, vl);
             pair_split(m, mh, ml);
             pair_split(h, hh, hl);
             pair_split(n, nh, nl);
+            if (t + 1 == next_ckpt && next_ckpt < a.ckpt_end && lane < R.active) {
+                const Seg &S = a.segs[R.seg];
+                const int64_t gid = (w_first + R.rel) * kWave + lane;
+                float *c = a.ckpt_state + (next_ckpt / a.ckpt_every) * 8 * a.n_waves * kWave + gid;
+                int64_t *cg = a.ckpt_G + (next_ckpt / a.ckpt_every) * a.g_stride;
+                const float pairs[8] = {vh, vl, mh, ml, hh, hl, nh, nl};
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (k < 4 || is_hh) c[k * a.n_waves * kWave] = pairs[k];
+#pragma unroll
+                for (int q = 0; q < kMaxIn; ++q)
+                    if (q < S.n_in) cg[S.in_G[q] + (gid - S.base)] = (int64_t)s_g[R.g_off[q] + lane];
+            }
             if (t + 1 < t_end) {
                 v = (double)vh + (double)vl;
                 m = (double)mh + (double)ml;
                 if (is_hh) {
-                    hh_ahead(S, x, v, m, (double)hh + (double)hl, (double)nh + (double)nl);
+                    hh_ahead(R, x, v, m, (double)hh + (double)hl, (double)nh + (double)nl);
                 } else {
                     x[0] = v;
                     x[kWave] = m;
                 }
-            } else if (active) {
+            } else if (lane < R.active) {
+                const Seg &S = a.segs[R.seg];
+                const int64_t gid = (w_first + R.rel) * kWave + lane;
                 a.vh[gid] = vh;
                 a.vl[gid] = vl;
                 a.mh[gid] = mh;
@@ -391,16 +537,26 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
                 }
 #pragma unroll
                 for (int q = 0; q < kMaxIn; ++q)
-                    if (q < n_in) a.G[S.in_G[q] + j] = (int64_t)s_g[W.g_off[q] + lane];
-                if (kRec && S.record_vbar) a.vsum[gid] = s_vsum[w * kWave + lane];
+                    if (q < S.n_in) a.G[S.in_G[q] + (gid - S.base)] = (int64_t)s_g[R.g_off[q] + lane];
+                if (kRec && R.rec) a.vsum[gid] = s_vsum[w * kWave + lane];
             }
         }
+        if (t + 1 == next_ckpt) next_ckpt += a.ckpt_every;
         if (t + 1 == t_end) break;
-        sources(t + 1, l_next);
-        const int l = l_prev;
-        l_prev = l_cur;
-        l_cur = l_next;
-        l_next = l;
+
+        // ---- the next step's sources; deliver S(t)
+        sources(t + 1);
+        if (help_i >= 0) {
+            const bool all = t < t0 || (multi && (late_feeds || (t & (kResCheck - 1)) == 0));
+            list_rows(t, all ? r_begin : e_begin, all ? r_end : e_end);
+        }
+        __syncthreads();
+        deliver_list(t);
+        __syncthreads();
+        if (multi && s_fail) {
+            if (threadIdx.x == 0) atomicOr(&a.st->overflow, 4u);
+            return;
+        }
     }
 
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -409,33 +565,89 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     }
 }
 
-// bounds[row][part] of one split projection: where each part of the post
-// population starts in the row (columns ascend within a row).
-__global__ void k_slice_bounds(ResSplit d, const int32_t *rp_pool, const int32_t *col_pool, const int32_t *starts,
-                               int32_t *out)
+// First entry of CSR row [lo, hi) with column >= lim (columns ascend).
+__device__ __forceinline__ int32_t first_at(const int32_t *col, int32_t lo, int32_t hi, int32_t lim)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t np = d.parts + 1;
-    if (i >= (int64_t)d.n_pre * np) return;
-    const int32_t row = (int32_t)(i / np), part = (int32_t)(i % np);
-    const int32_t *rp = rp_pool + d.rp_base;
-    const int32_t *col = col_pool + d.syn_base;
-    int32_t lo = rp[row], hi = rp[row + 1];
-    const int32_t lim = starts[d.start0 + part];
     while (lo < hi) {
         const int32_t mid = lo + (hi - lo) / 2;
         if (col[mid] < lim) lo = mid + 1; else hi = mid;
     }
-    out[d.out0 + i] = lo;
+    return lo;
 }
 
-hipError_t launch_slice_bounds(const ResSplit &d, const int32_t *rp_pool, const int32_t *col_pool,
-                               const int32_t *starts, int32_t *out, hipStream_t s)
+// A block's slices of its feeds' rows: where each begins in the projection's
+// CSR (from) and, one after another, in the block's own synapses (bounds).
+__global__ __launch_bounds__(1024) void k_resident_bounds(const ResBlock *blocks, const ResSource *srcs,
+                                                          const int32_t *rp_pool, const int32_t *col_pool,
+                                                          int32_t *bounds, int32_t *from, int64_t *totals)
 {
-    const int64_t n = (int64_t)d.n_pre * (d.parts + 1);
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_slice_bounds, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, d, rp_pool, col_pool, starts,
-                       out);
+    __shared__ uint32_t s_sum[16];
+    const ResBlock &B = blocks[blockIdx.x];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    int64_t total = 0;
+    for (int f = 0; f < B.n_feed; ++f) {
+        const ResSource &F = srcs[B.feed0 + f];
+        const int32_t *rp = rp_pool + F.rp_base, *col = col_pool + F.syn_base;
+        for (int32_t r0 = 0; r0 < F.n_pre; r0 += blockDim.x) {
+            const int32_t r = r0 + threadIdx.x;
+            uint32_t len = 0;
+            if (r < F.n_pre) {
+                const int32_t a = first_at(col, rp[r], rp[r + 1], F.c0), b = first_at(col, a, rp[r + 1], F.c1);
+                from[F.bounds0 + r] = a;
+                len = (uint32_t)(b - a);
+            }
+            const uint32_t incl = wave_incl_sum(len, lane);
+            if (lane == kWave - 1) s_sum[wid] = incl;
+            __syncthreads();
+            uint32_t before = 0, all = 0;
+            for (int w = 0; w < nw; ++w) {
+                if (w < wid) before += s_sum[w];
+                all += s_sum[w];
+            }
+            if (r < F.n_pre) bounds[F.bounds0 + r] = (int32_t)(total + before + incl - len);
+            total += all;
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) bounds[F.bounds0 + F.n_pre] = (int32_t)total;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = total;
+}
+
+// The blocks' synapses (LDS conductance, weight) from the CSR pools; a
+// wavefront per slice, grid (blocks, any).
+__global__ __launch_bounds__(256) void k_resident_fill(const ResBlock *blocks, const ResSource *srcs,
+                                                       const int32_t *col_pool, const float *w_pool,
+                                                       const int32_t *bounds, const int32_t *from, int2 *syn)
+{
+    const ResBlock &B = blocks[blockIdx.x];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = (int)(blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6)), nw = (int)(gridDim.y * (blockDim.x >> 6));
+    for (int f = 0; f < B.n_feed; ++f) {
+        const ResSource &F = srcs[B.feed0 + f];
+        const int32_t *col = col_pool + F.syn_base;
+        const float *w = w_pool + F.syn_base;
+        for (int32_t r = wave; r < F.n_pre; r += nw) {
+            const int32_t b0 = bounds[F.bounds0 + r], b1 = bounds[F.bounds0 + r + 1], k0 = from[F.bounds0 + r];
+            for (int32_t k = lane; k < b1 - b0; k += kWave)
+                syn[B.syn0 + b0 + k] = make_int2(F.g0 + col[k0 + k], __float_as_int(w[k0 + k]));
+        }
+    }
+}
+
+hipError_t launch_resident_bounds(const ResBlock *blocks, int n, const ResSource *srcs, const int32_t *rp_pool,
+                                  const int32_t *col_pool, int32_t *bounds, int32_t *from, int64_t *totals, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_resident_bounds, dim3((unsigned)n), dim3(1024), 0, s, blocks, srcs, rp_pool, col_pool, bounds,
+                       from, totals);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_fill(const ResBlock *blocks, int n, const ResSource *srcs, const int32_t *col_pool,
+                                const float *w_pool, const int32_t *bounds, const int32_t *from, int2 *syn, hipStream_t s)
+{
+    const int y = std::max(1, std::min(256, 4096 / n));
+    hipLaunchKernelGGL(k_resident_fill, dim3((unsigned)n, (unsigned)y), dim3(256), 0, s, blocks, srcs, col_pool, w_pool,
+                       bounds, from, syn);
     return hipGetLastError();
 }
 

@@ -144,8 +144,10 @@ struct ResidentPlan {
     ResBlock *d_blocks;
     ResWord *d_words;
     ResFeed *d_feeds;
-    uint32_t *d_wfeeds;
-    int32_t *d_bounds;
+    ResSource *d_sources;
+    uint32_t *d_wfeeds, *d_reads;
+    int32_t *d_bounds, *d_from;
+    int2 *d_syn;
     uint64_t *d_xbuf;
 };
 
@@ -204,6 +206,7 @@ struct snn_net {
     int2 *d_grp_proj;        // grouped mode: (projection, rows per group) of those delivered in groups
     int64_t n_grp;
     int64_t pull_count;      // packets
+    bool pull_stale;         // d_pull_w holds older weights than the pool
     uint32_t *pullf;     // arena: [2][n_segs]  populations delivered by pulling
     uint32_t *awcnt;     // arena: [2][n_segs]
     uint32_t *scnt;      // arena: [2][n_segs]
@@ -547,8 +550,9 @@ int pending_to_bits(snn_net *net)
     return SNN_OK;
 }
 
-int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps)
+int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps, int64_t ckpt_every = 0)
 {
+    const int64_t ckpt_end = net->t + n;
     int rc = pending_to_bits(net);
     if (rc) return rc;
     const NeuronArgs na = neuron_args(net);
@@ -558,6 +562,8 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     a.words = net->res.d_words;
     a.feeds = net->res.d_feeds;
     a.wfeeds = net->res.d_wfeeds;
+    a.reads = net->res.d_reads;
+    a.syn = net->res.d_syn;
     a.xbuf = net->res.d_xbuf;
     a.vh = net->vh; a.vl = net->vl; a.mh = net->mh; a.ml = net->ml;
     a.hh = net->hh; a.hl = net->hl; a.nh = net->nh; a.nl = net->nl;
@@ -571,12 +577,15 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     a.raster_steps = raster_steps;
     a.substeps = net->substeps;
     a.hs = na.hs;
-    a.col_pool = net->d_col;
-    a.w_pool = net->d_w;
     a.gscale = net->d_gscale;
     a.izp = net->d_izp;
     a.st = net->st;
     a.max_wait = (int64_t)20 * 100000000;   // 20 s of the 100 MHz wall clock
+    a.ckpt_every = ckpt_every;
+    a.ckpt_end = ckpt_end;
+    a.ckpt_state = net->d_ckpt_state;
+    a.ckpt_G = net->d_ckpt_G;
+    a.g_stride = std::max<int64_t>(net->G_count, 1);
     while (n > 0) {
         a.t0 = net->t;
         a.n = std::min(n, kResidentLaunch);
@@ -1655,15 +1664,18 @@ int snn_get_last_spikes(snn_net *net, int32_t inst, int32_t pop, uint8_t *out)
 
 // ------------------------------ resident plan --------------------------------
 // Deals the words of every instance out over the blocks of its cluster and
-// builds the blocks' tables.  More blocks shorten the update (four words, one
-// per SIMD, take 1.9 us; each further word on a SIMD 0.9) and lengthen the
-// exchange (0.9 us and 4 ns per word of the instance, measured), so the words
-// per block are chosen by that estimate, over all sizes whose blocks are
-// resident together at one per CU; a network of more instances than that
-// keeps each in one block, any number of them.  Networks that do not fit (LDS:
-// 2.6 to 4 KiB per word), with plastic projections, or whose estimate is not
-// below the step kernels' (7 us and 2.5 ns per word, measured on batches of 20 to
-// 256 instances) keep the step kernels.
+// builds the blocks' tables.  A step takes a block about as long for one word
+// as for one per SIMD, and then longer with every word, while more blocks
+// lengthen the exchange little: 1 100 neurons take 3.6 us a step in 5 blocks,
+// 4.6 in 3, 5.5 in 2, 7.4 in one; 21 000 take 5.7 in 84, 6.8 in 56, 7.7 in 42,
+// 9.2 in 24; a sweep of 100 networks 7.6 in 200, 11.5 in 100.  So the blocks
+// are as many as are resident together at one per compute unit, down to four
+// words each; where the instances alone are more, each keeps to one block.
+// Networks that do not fit (LDS: 3.2 to 5 KiB per word), with plastic
+// projections, or whose estimate (2 us, and 4 for every 16 words of a block,
+// times the blocks per compute unit) is not below the step kernels' (7 us and
+// 2.5 ns per word, measured on batches of 20 to 256 instances) keep the step
+// kernels.
 static int plan_resident(snn_net *net)
 {
     ResidentPlan &R = net->res;
@@ -1677,10 +1689,24 @@ static int plan_resident(snn_net *net)
         return SNN_OK;
     }
     const int n_cu = prop.multiProcessorCount;
-    constexpr int64_t kLds = 156 * 1024;
+    constexpr int64_t kLds = 160 * 1024 - 512;   // (the kernel has a few words of its own)
 
-    struct Inst { int64_t w_first, n_words, n_state, n_poi, syn_first, nnz; double load; };
+    struct Inst { int64_t w_first, n_words, n_state, n_poi, nnz; double load, read_load; };
     std::vector<Inst> in(net->n_inst);
+    auto reads_neurons = [&](const Seg &S) {
+        for (int q = 0; q < S.n_in; ++q) {
+            const Proj &P = net->projs[S.in_proj[q]];
+            if (P.nnz > 0 && net->segs[P.pre_seg].kind != kPoisson) return true;
+        }
+        return false;
+    };
+    // a word's part of its block's time, in updates of 64 Traub-Miles neurons:
+    // those that neurons project to receive far more synapses than the
+    // others (a row of sources spikes at the sources' rate)
+    auto word_load = [&](const Seg &S) {
+        if (S.kind == kPoisson) return 0.3;
+        return (S.kind == kHH ? 1.0 : 0.3) + (reads_neurons(S) ? 1.5 : 0.0);
+    };
     double step_kernels = 7.0;
     for (int b = 0; b < net->n_inst; ++b) {
         Inst &I = in[b];
@@ -1692,12 +1718,12 @@ static int plan_resident(snn_net *net)
             const int64_t w = align_up(S.n, kWave) / kWave;
             I.n_words += w;
             (S.kind == kPoisson ? I.n_poi : I.n_state) += w;
-            I.load += (double)w * (S.kind == kHH ? 1.0 : 0.3);
+            I.load += (double)w * word_load(S);
+            if (S.kind != kPoisson && reads_neurons(S)) I.read_load += (double)w * word_load(S);
             step_kernels += 0.0025 * (double)w * (S.kind == kHH ? 1.0 : 0.3);
         }
         for (size_t k = 0; k < net->proj_of[b].size(); ++k) {
             const Proj &P = net->projs[net->proj_of[b][k]];
-            if (k == 0) I.syn_first = P.syn_base;
             I.nnz += P.nnz;
         }
         if (I.n_words == 0 || I.n_words > ((int64_t)1 << 20) || I.nnz >= ((int64_t)1 << 31)) return SNN_OK;
@@ -1722,6 +1748,9 @@ static int plan_resident(snn_net *net)
             const int M = (int)std::min<int64_t>(std::max<int64_t>(1, (int64_t)std::ceil(I.load / per_block)), I.n_words);
             L.first.push_back((int)L.blocks);
             L.n.push_back(M);
+            const int Mr = M < 4 || I.read_load <= 0.0 || I.read_load >= I.load - 0.3 * (double)I.n_poi - 0.5
+                               ? 0
+                               : std::min(M - 1, (int)std::ceil(M * I.read_load / I.load));
             std::vector<double> load(M, 0.0);
             std::vector<int64_t> st(M, 0), po(M, 0), g(M, 0), feeds(M, 0);
             std::vector<int> segs(net->seg_of[b].begin(), net->seg_of[b].end());
@@ -1730,16 +1759,21 @@ static int plan_resident(snn_net *net)
                        std::make_pair(net->segs[y].kind == kPoisson, -net->segs[y].n);
             });
             for (int s : segs) {
-                // equal parts, the remainder to the least loaded blocks
+                // equal parts, the remainder to the least loaded blocks; in a
+                // larger cluster, populations that read neurons' spikes have
+                // blocks of their own, so that the others need not wait for
+                // them (they only read them to keep within the ring)
                 const Seg &S = net->segs[s];
                 const int64_t w = align_up(S.n, kWave) / kWave;
-                const double c = S.kind == kHH ? 1.0 : 0.3;
+                const double c = word_load(S);
+                const bool reads = S.kind != kPoisson && reads_neurons(S);
+                const int r0 = Mr == 0 || reads ? 0 : Mr, r1 = Mr > 0 && reads ? Mr : M, Mp = r1 - r0;
                 std::vector<int32_t> &sh = L.share[s];
-                sh.assign(M, (int32_t)(w / M));
-                std::vector<int> order(M);
-                for (int r = 0; r < M; ++r) order[r] = r;
+                sh.assign(M, 0);
+                std::vector<int> order(Mp);
+                for (int r = 0; r < Mp; ++r) order[r] = r0 + r;
                 std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return load[x] < load[y]; });
-                for (int64_t r = 0; r < w % M; ++r) sh[order[r]]++;
+                for (int r = 0; r < Mp; ++r) sh[order[r]] = (int32_t)(w / Mp) + (r < w % Mp ? 1 : 0);
                 for (int r = 0; r < M; ++r) {
                     load[r] += c * sh[r];
                     (S.kind == kPoisson ? po[r] : st[r]) += sh[r];
@@ -1752,18 +1786,15 @@ static int plan_resident(snn_net *net)
                     }
                 }
             }
-            const double exchange = M > 1 ? 0.9 + 0.004 * (double)I.n_words : 0.0;
             split |= M > 1;
             for (int r = 0; r < M; ++r) {
                 if (feeds[r] >= (1 << 16)) return L.blocks = 0, L;
                 L.state.push_back(st[r]);
                 L.poi.push_back(po[r]);
-                L.lds.push_back(24 * g[r] + 20 * I.n_words + 12 * kResList + ((feat & kFeatRec) ? 3072 : 2560) * st[r] +
-                                (int64_t)sizeof(ResFeed) * feeds[r]);
+                L.lds.push_back(8 * g[r] + (kResNeuronRec + 2560 + ((feat & kFeatRec) ? 512 : 0)) * st[r] +
+                                kResSourceRec * po[r] + 24 * I.n_words + 4 * kResList + (int64_t)sizeof(ResFeed) * feeds[r]);
                 worst_lds = std::max(worst_lds, L.lds.back());
-                const double rounds = std::ceil((double)st[r] / 16.0), src = 0.35 * std::ceil((double)po[r] / 16.0);
-                const double t = 1.5 * rounds + std::max(exchange, 0.8 * rounds + src) + 1.0;
-                worst = std::max(worst, t);
+                worst = std::max(worst, 2.0 + 4.0 * std::ceil((double)st[r] / 16.0));
             }
             L.blocks += M;
         }
@@ -1774,25 +1805,20 @@ static int plan_resident(snn_net *net)
         return L;
     };
     Layout best;
-    for (double per : {4.0, 5.0, 6.0, 7.0, 8.0, 10.0, 12.0, 14.0, 16.0, 20.0, 24.0, 28.0, 32.0, 40.0, 48.0, 64.0}) {
-        Layout L = lay_out(per);
-        if (L.blocks > 0 && (best.blocks == 0 || L.cost < best.cost)) best = std::move(L);
-    }
+    for (double per = 4.0; best.blocks == 0 && per < 64.0; per *= 1.05) best = lay_out(per);
     if (best.blocks == 0 || best.cost > step_kernels) return SNN_OK;
 
     // ---- the tables
     std::vector<ResBlock> blocks;
     std::vector<ResWord> words;
     std::vector<ResFeed> feeds;
-    std::vector<int64_t> feed_bounds;        // offset into the built bounds, -1: the row pointers
+    std::vector<ResSource> sources;
     std::vector<uint32_t> wfeeds;
-    std::vector<ResSplit> splits;
-    std::vector<int32_t> starts;             // first neuron of each part of each split projection
-    int64_t x_total = 0, bounds_total = 0, max_lds = 0, max_state = 0;
+    std::vector<uint32_t> reads;
+    int64_t x_total = 0, bounds_total = 0, syn_total = 0, max_lds = 0;
     for (int b = 0; b < net->n_inst; ++b) {
         const Inst &I = in[b];
         const int M = best.n[b];
-        std::vector<int64_t> built(net->proj_of[b].size() + 1, -1);
         for (int r = 0; r < M; ++r) {
             ResBlock B{};
             B.inst = b;
@@ -1802,7 +1828,7 @@ static int plan_resident(snn_net *net)
             B.word0 = (int64_t)words.size();
             B.wfeed0 = (int64_t)wfeeds.size();
             B.feed0 = (int64_t)feeds.size();
-            B.syn_first = I.syn_first;
+            B.read0 = (int64_t)reads.size();
             B.x_off = x_total;
             std::vector<int> pre;                         // pre population of each of its feeds
             for (int pass = 0; pass < 2; ++pass)          // words with a membrane first
@@ -1812,11 +1838,7 @@ static int plan_resident(snn_net *net)
                     const std::vector<int32_t> &sh = best.share[s];
                     if (sh[r] == 0) continue;
                     int64_t w0 = 0;
-                    int part = 0, parts = 0;
-                    for (int k = 0; k < M; ++k) {
-                        if (k < r) w0 += sh[k], part += sh[k] > 0;
-                        parts += sh[k] > 0;
-                    }
+                    for (int k = 0; k < r; ++k) w0 += sh[k];
                     std::vector<int64_t> g0(S.n_in);
                     for (int q = 0; q < S.n_in; ++q) {
                         const Proj &P = net->projs[S.in_proj[q]];
@@ -1824,31 +1846,22 @@ static int plan_resident(snn_net *net)
                         B.n_g += sh[r] * kWave;
                         if (P.nnz == 0) continue;
                         ResFeed F{};
-                        F.stride = parts > 1 ? parts + 1 : 1;
-                        F.syn = (int32_t)(P.syn_base - I.syn_first);
-                        F.g0 = (int32_t)(g0[q] - w0 * kWave);
                         F.word0 = (int32_t)(net->segs[P.pre_seg].base / kWave - I.w_first);
-                        int64_t off = -1;
-                        if (parts > 1) {
-                            int64_t &at = built[std::find(net->proj_of[b].begin(), net->proj_of[b].end(), S.in_proj[q]) -
-                                                net->proj_of[b].begin()];
-                            if (at < 0) {
-                                at = bounds_total;
-                                splits.push_back(ResSplit{P.rp_base, P.syn_base, at, (int64_t)starts.size(), P.n_pre, parts});
-                                int64_t w = 0;
-                                for (int k = 0; k < M; ++k)
-                                    if (sh[k] > 0) {
-                                        starts.push_back((int32_t)(w * kWave));
-                                        w += sh[k];
-                                    }
-                                starts.push_back(INT32_MAX);
-                                bounds_total += (int64_t)P.n_pre * (parts + 1);
-                            }
-                            off = at + part;
-                        }
-                        feed_bounds.push_back(off >= 0 ? off : -1 - P.rp_base);
+                        F.n_pre = P.n_pre;
+                        F.lds = -1;
+                        if (net->segs[P.pre_seg].kind != kPoisson) B.late_feeds = 1;
+                        ResSource Q{};
+                        Q.rp_base = P.rp_base;
+                        Q.syn_base = P.syn_base;
+                        Q.bounds0 = bounds_total;
+                        Q.n_pre = P.n_pre;
+                        Q.c0 = (int32_t)(w0 * kWave);
+                        Q.c1 = (int32_t)std::min<int64_t>((w0 + sh[r]) * kWave, S.n);
+                        Q.g0 = (int32_t)(g0[q] - w0 * kWave);
+                        bounds_total += P.n_pre + 1;
                         pre.push_back(P.pre_seg);
                         feeds.push_back(F);
+                        sources.push_back(Q);
                         B.n_feed++;
                     }
                     for (int32_t k = 0; k < sh[r]; ++k) {
@@ -1865,11 +1878,11 @@ static int plan_resident(snn_net *net)
             for (int k = 0; k < B.n_feed; ++k) by[k] = k;
             std::stable_sort(by.begin(), by.end(), [&](int x, int y) { return pre[x] < pre[y]; });
             const std::vector<ResFeed> f(feeds.begin() + B.feed0, feeds.end());
-            const std::vector<int64_t> fb(feed_bounds.begin() + B.feed0, feed_bounds.end());
+            const std::vector<ResSource> fs(sources.begin() + B.feed0, sources.end());
             wfeeds.resize(B.wfeed0 + I.n_words, 0u);
             for (int k = 0; k < B.n_feed; ++k) {
                 feeds[B.feed0 + k] = f[by[k]];
-                feed_bounds[B.feed0 + k] = fb[by[k]];
+                sources[B.feed0 + k] = fs[by[k]];
                 const Seg &S = net->segs[pre[by[k]]];
                 for (int64_t w = 0; w < align_up(S.n, kWave) / kWave; ++w) {
                     uint32_t &e = wfeeds[B.wfeed0 + f[by[k]].word0 + w];
@@ -1877,15 +1890,42 @@ static int plan_resident(snn_net *net)
                     ++e;
                 }
             }
-            max_state = std::max<int64_t>(max_state, B.n_state);
+            for (int pass = 0; pass < 2; ++pass)
+                for (int sg : net->seg_of[b]) {
+                    const Seg &S = net->segs[sg];
+                    if ((S.kind == kPoisson) != (pass == 0)) continue;
+                    for (int64_t w = 0; w < align_up(S.n, kWave) / kWave; ++w) {
+                        const int64_t rel = S.base / kWave - I.w_first + w;
+                        if (pass == 0 && wfeeds[B.wfeed0 + rel] == 0) continue;
+                        reads.push_back((uint32_t)rel);
+                        (pass == 0 ? B.n_early : B.n_late)++;
+                    }
+                }
             blocks.push_back(B);
         }
         if (M > 1) x_total += (int64_t)kResRing * 2 * I.n_words;
         R.together |= M > 1;
     }
-    for (int64_t l : best.lds) max_lds = std::max(max_lds, l);
     R.blocks = (int)best.blocks;
-    R.block = kWave * (int)std::min<int64_t>(16, std::max<int64_t>(8, align_up(max_state, 4)));
+    // slice bounds in LDS as far as they fit, neurons' first
+    const int64_t room = R.blocks > n_cu ? kLds / 2 : kLds;
+    for (size_t k = 0; k < blocks.size(); ++k) {
+        int64_t used = align_up(best.lds[k], 8), at = 0;
+        for (int pass = 0; pass < 2; ++pass)
+            for (int f = 0; f < blocks[k].n_feed; ++f) {
+                ResFeed &F = feeds[blocks[k].feed0 + f];
+                bool poisson = false;
+                for (int sg : net->seg_of[blocks[k].inst])
+                    if (net->segs[sg].base / kWave - blocks[k].w_first == F.word0) poisson |= net->segs[sg].kind == kPoisson;
+                if (poisson != (pass == 1) || used + 4 * (at + F.n_pre + 1) > room) continue;
+                F.lds = (int32_t)at;
+                at += F.n_pre + 1;
+            }
+        max_lds = std::max(max_lds, used + 4 * at);
+    }
+    // all of a compute unit's wavefronts (4 per SIMD): those without a word
+    // read the others' spikes; half of them where two blocks share the unit
+    R.block = kWave * (R.blocks > n_cu ? 8 : 16);
     R.lds = (size_t)align_up(max_lds, 256);
     if (!resident_fits(feat, R.block, R.lds, R.blocks, R.together, n_cu)) return SNN_OK;
     // single blocks end at their own times: the longest first
@@ -1897,22 +1937,39 @@ static int plan_resident(snn_net *net)
     R.d_words = (ResWord *)dev_alloc(net, sizeof(ResWord) * words.size());
     R.d_feeds = (ResFeed *)dev_alloc(net, sizeof(ResFeed) * std::max<size_t>(feeds.size(), 1));
     R.d_wfeeds = (uint32_t *)dev_alloc(net, 4 * std::max<size_t>(wfeeds.size(), 1));
+    R.d_sources = (ResSource *)dev_alloc(net, sizeof(ResSource) * std::max<size_t>(feeds.size(), 1));
+    R.d_reads = (uint32_t *)dev_alloc(net, 4 * std::max<size_t>(reads.size(), 1));
     R.d_bounds = (int32_t *)dev_alloc(net, 4 * (size_t)std::max<int64_t>(bounds_total, 1));
+    R.d_from = (int32_t *)dev_alloc(net, 4 * (size_t)std::max<int64_t>(bounds_total, 1));
+    R.d_syn = (int2 *)dev_alloc(net, sizeof(int2) * (size_t)std::max<int64_t>(net->w_count, 1));
     R.d_xbuf = (uint64_t *)dev_alloc(net, 8 * (size_t)std::max<int64_t>(x_total, 1));
-    int32_t *d_starts = (int32_t *)dev_alloc(net, 4 * std::max<size_t>(starts.size(), 1));
-    if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_bounds || !R.d_xbuf || !d_starts)
+    int64_t *d_totals = (int64_t *)dev_alloc(net, 8 * blocks.size());
+    if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_sources || !R.d_reads || !R.d_bounds || !R.d_from ||
+        !R.d_syn || !R.d_xbuf || !d_totals)
         return fail(SNN_ENOMEM, "device allocation failed");
-    for (size_t k = 0; k < feeds.size(); ++k)
-        feeds[k].bounds = feed_bounds[k] >= 0 ? R.d_bounds + feed_bounds[k] : net->d_rp + (-1 - feed_bounds[k]);
+    for (size_t k = 0; k < feeds.size(); ++k) feeds[k].bounds = R.d_bounds + sources[k].bounds0;
     int rc;
     if ((rc = h2d(net, R.d_blocks, blocks.data(), sizeof(ResBlock) * blocks.size()))) return rc;
     if ((rc = h2d(net, R.d_words, words.data(), sizeof(ResWord) * words.size()))) return rc;
     if ((rc = h2d(net, R.d_feeds, feeds.data(), sizeof(ResFeed) * feeds.size()))) return rc;
+    if ((rc = h2d(net, R.d_sources, sources.data(), sizeof(ResSource) * sources.size()))) return rc;
     if ((rc = h2d(net, R.d_wfeeds, wfeeds.data(), 4 * wfeeds.size()))) return rc;
-    if ((rc = h2d(net, d_starts, starts.data(), 4 * starts.size()))) return rc;
+    if ((rc = h2d(net, R.d_reads, reads.data(), 4 * reads.size()))) return rc;
     HIP_OK(launch_fill_zero(R.d_xbuf, 8 * (size_t)std::max<int64_t>(x_total, 1), net->stream));
-    for (const ResSplit &d : splits)
-        HIP_OK(launch_slice_bounds(d, net->d_rp, net->d_col, d_starts, R.d_bounds, net->stream));
+    HIP_OK(launch_resident_bounds(R.d_blocks, R.blocks, R.d_sources, net->d_rp, net->d_col, R.d_bounds, R.d_from, d_totals,
+                                  net->stream));
+    std::vector<int64_t> totals(blocks.size());
+    if ((rc = d2h(net, totals.data(), d_totals, 8 * totals.size()))) return rc;
+    dev_free(net, d_totals);
+    for (size_t k = 0; k < blocks.size(); ++k) {
+        if (totals[k] >= ((int64_t)1 << 31)) return SNN_OK;
+        blocks[k].syn0 = syn_total;
+        syn_total += totals[k];
+    }
+    if (syn_total > net->w_count) return fail(SNN_EDEVICE, "resident synapses exceed the pool (internal)");
+    if ((rc = h2d(net, R.d_blocks, blocks.data(), sizeof(ResBlock) * blocks.size()))) return rc;
+    HIP_OK(launch_resident_fill(R.d_blocks, R.blocks, R.d_sources, net->d_col, net->d_w, R.d_bounds, R.d_from, R.d_syn,
+                                net->stream));
     HIP_OK(hipStreamSynchronize(net->stream));
     R.ok = R.on = true;
     return SNN_OK;
@@ -2297,6 +2354,16 @@ int snn_get_launch(const snn_net *net, snn_launch *out)
     return SNN_OK;
 }
 
+// Weights of the column copies that tile mode pulls from.
+static int refresh_pull(snn_net *net)
+{
+    if (!net->pull_stale) return SNN_OK;
+    HIP_OK(launch_gather_weights(net->d_w, net->d_pull_perm, (float *)net->d_pull_w, 4 * kWave * net->pull_count,
+                                 net->stream));
+    net->pull_stale = false;
+    return SNN_OK;
+}
+
 int snn_set_launch(snn_net *net, const snn_launch *in)
 {
     int rc = check_net(net);
@@ -2318,6 +2385,7 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
     const snn_launch prev = net->launch;
     net->launch = *in;
     net->res.on = false;      // a shape given by the caller is the one that runs
+    if (in->mode == kModeTiles && (rc = refresh_pull(net))) return rc;
     if ((rc = update_qbuckets(net))) return rc;
     if (net->pend_bits) {
         if ((rc = materialize(net))) return rc;
@@ -2504,8 +2572,12 @@ int snn_set_weights_device(snn_net *net, const float *src)
             return fail(SNN_ERANGE, "projection %zu: g_scale * column sum / (1 - decay) exceeds %g uS", q, kGLimit);
     }
     HIP_OK(hipMemcpyAsync(net->d_w, src, 4 * (size_t)net->w_count, hipMemcpyDeviceToDevice, net->stream));
-    HIP_OK(launch_gather_weights(net->d_w, net->d_pull_perm, (float *)net->d_pull_w, 4 * kWave * net->pull_count,
-                                 net->stream));
+    // the copies that the steps use; tile mode's also on a switch to it
+    net->pull_stale = true;
+    if (net->launch.mode == kModeTiles && !net->res.on && (rc = refresh_pull(net))) return rc;
+    if (net->res.on)
+        HIP_OK(launch_resident_fill(net->res.d_blocks, net->res.blocks, net->res.d_sources, net->d_col, net->d_w,
+                                    net->res.d_bounds, net->res.d_from, net->res.d_syn, net->stream));
     if (net->launch.mode != kModeFused || net->pend_bits) return SNN_OK;
     // fused mode: the pending deliveries of S(t-1) were made with the old
     // weights; the other modes deliver them at step t with the new ones
@@ -2603,7 +2675,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     na.raster = net->d_rec_raster;
     na.raster_steps = (int32_t)T;
     const PropArgs pa = prop_args(net);
-    const bool resident = use_resident(net, K);
+    const bool resident = use_resident(net, T);
     for (int64_t t = 0; t < T; ++t) {
         if (t % K == 0) {
             const int64_t sgi = t / K;
@@ -2613,10 +2685,9 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
                                   8 * (size_t)net->G_count, hipMemcpyDeviceToDevice, net->stream));
         }
         if (resident) {
-            const int64_t k = std::min(K, T - t);
-            if ((rc = run_resident(net, k, net->d_rec_raster, (int32_t)T))) return rc;
-            t += k - 1;
-            continue;
+            // the later checkpoints are left on the way
+            if ((rc = run_resident(net, T, net->d_rec_raster, (int32_t)T, K))) return rc;
+            break;
         }
         HIP_OK(launch_propagate(pa, net->launch.prop_blocks, net->launch.prop_block, net->stream));
         HIP_OK(launch_neuron(na, net->launch.neuron_block, net->stream));
