@@ -481,6 +481,8 @@ hipError_t launch_potentiate(const LtpArgs &a, int blocks, int block, hipStream_
 hipError_t launch_gather_weights(const float *w, const int32_t *perm, float *out, int64_t n, hipStream_t s);
 hipError_t launch_spike_totals(const Seg *segs, int32_t n_segs, const int32_t *counts, int32_t pop, int64_t *out,
                                hipStream_t s);
+// na + nb words of a and b into host memory `out` (its device address).
+hipError_t launch_read_words(const uint32_t *a, int64_t na, const uint32_t *b, int64_t nb, uint32_t *out, hipStream_t s);
 // Zero `bytes` (a multiple of 4) at p with a kernel.
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_check_weights(const float *w, const Proj *projs, int32_t n_projs, int64_t max_nnz, uint32_t *flag,

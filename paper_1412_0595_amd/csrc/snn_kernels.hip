@@ -1553,6 +1553,21 @@ hipError_t launch_potentiate(const LtpArgs &a, int blocks, int block, hipStream_
     return hipGetLastError();
 }
 
+// Two arrays of 32-bit words, one after the other, into host memory.
+__global__ __launch_bounds__(256) void k_read_words(const uint32_t *a, int64_t na, const uint32_t *b, int64_t nb,
+                                                    uint32_t *out)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = i < na ? a[i] : b[i - na];
+}
+
+hipError_t launch_read_words(const uint32_t *a, int64_t na, const uint32_t *b, int64_t nb, uint32_t *out, hipStream_t s)
+{
+    const int64_t blocks = std::min<int64_t>((na + nb + 255) / 256, 256);
+    hipLaunchKernelGGL(k_read_words, dim3((unsigned)blocks), dim3(256), 0, s, a, na, b, nb, out);
+    return hipGetLastError();
+}
+
 // Zero n_words 32-bit words with a kernel (a fill inside a captured graph
 // stays a kernel node; no memset node): 16-byte stores over the aligned body
 // when p is 16-byte aligned, 4-byte stores for the rest.
