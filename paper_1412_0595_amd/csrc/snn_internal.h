@@ -316,6 +316,11 @@ struct PropArgs {
     const int32_t *pull_r0;  // [unit][64] lane's row before the unit's first entry
     const int2 *grp_proj;    // grouped mode: (projection, rows per group) of those delivered in groups
     int64_t n_grp;           // 0 unless grouped mode
+    int32_t ltp;             // 1: rows mode does the potentiation too (the fields of LtpArgs; no event pair)
+    const Item *lqueue;
+    int64_t lcap;
+    const int32_t *csc_row;
+    const int32_t *csc_pos;
 };
 
 struct LtpArgs {

@@ -434,6 +434,10 @@ PropArgs prop_args(snn_net *net)
     p.pull_d = net->d_pull_d;
     p.pull_r0 = net->d_pull_r0;
     p.n_segs = (int32_t)net->segs.size();
+    p.lqueue = net->lqueue;
+    p.lcap = net->lcap;
+    p.csc_row = net->d_csc_row;
+    p.csc_pos = net->d_csc_pos;
     return p;
 }
 
@@ -456,9 +460,11 @@ hipError_t enqueue_step(snn_net *net, hipStream_t s)
 {
     // fused mode: the neuron update delivers its own spikes
     if (net->launch.mode == kModeFused) return launch_neuron(neuron_args(net), net->launch.neuron_block, s);
-    hipError_t e = launch_propagate(prop_args(net), net->launch.prop_blocks, net->launch.prop_block, s);
+    PropArgs p = prop_args(net);
+    p.ltp = net->plastic && p.mode == kModeRows ? 1 : 0;
+    hipError_t e = launch_propagate(p, net->launch.prop_blocks, net->launch.prop_block, s);
     if (e != hipSuccess) return e;
-    if (net->plastic) {
+    if (net->plastic && !p.ltp) {
         e = launch_potentiate(ltp_args(net), net->launch.prop_blocks, net->launch.prop_block, s);
         if (e != hipSuccess) return e;
     }
