@@ -1734,11 +1734,12 @@ static int plan_resident(snn_net *net)
         return false;
     };
     // a word's part of its block's time, in updates of 64 Traub-Miles neurons:
-    // those that neurons project to receive far more synapses than the
-    // others (a row of sources spikes at the sources' rate)
+    // those that neurons project to receive more synapses and are on the
+    // longer chain (21 000 neurons: 5.6, 5.3 and 4.8 us a step with 0.5, 1.5
+    // and 3 more for them)
     auto word_load = [&](const Seg &S) {
         if (S.kind == kPoisson) return 0.3;
-        return (S.kind == kHH ? 1.0 : 0.3) + (reads_neurons(S) ? 1.5 : 0.0);
+        return (S.kind == kHH ? 1.0 : 0.3) + (reads_neurons(S) ? 3.0 : 0.0);
     };
     double step_kernels = 7.0;
     for (int b = 0; b < net->n_inst; ++b) {
@@ -1781,6 +1782,9 @@ static int plan_resident(snn_net *net)
             const int M = (int)std::min<int64_t>(std::max<int64_t>(1, (int64_t)std::ceil(I.load / per_block)), I.n_words);
             L.first.push_back((int)L.blocks);
             L.n.push_back(M);
+            // blocks for the populations that read neurons (a batch of 48 uneven
+            // networks 13.3 us a step; 15.2 with those whose share does not
+            // fill a block mixed into the others)
             const int Mr = M < 4 || I.read_load <= 0.0 || I.read_load >= I.load - 0.3 * (double)I.n_poi - 0.5
                                ? 0
                                : std::min(M - 1, (int)std::ceil(M * I.read_load / I.load));
