@@ -23,6 +23,8 @@
 // recomputed a segment step by step, one lane per neuron that reversed it, one
 // wavefront per word that read the raster a step at a time took 10.9, 6.0 and
 // 2.6 us per step of 64 instances of 200 loss neurons.)
+#include <algorithm>
+
 #include "snn_device.h"
 
 namespace snn {
@@ -88,13 +90,14 @@ __device__ __forceinline__ void hh_substep_jvp(const Seg &S, double hs, double h
 // the wavefronts walk the words themselves.
 // ---------------------------------------------------------------------------
 constexpr int kAdjList = 1024;
+constexpr int kAdjSteps = 32768;   // steps per launch (a grid's second dimension is 16 bits)
 
 __global__ __launch_bounds__(256) void k_adj_deliver(AdjArgs a)
 {
     extern __shared__ long long s_inc[];      // [n_in][n]
     __shared__ int2 s_rows[kAdjList];         // (input, row)
     __shared__ uint32_t s_n;
-    const int b = blockIdx.x, k = blockIdx.y;
+    const int b = blockIdx.x, k = a.k_first + blockIdx.y;
     const int64_t t = a.t_a + k;
     const Seg &S = a.segs[a.loss_seg[b]];
     const int n = S.n, n_in = S.n_in;
@@ -413,7 +416,10 @@ __global__ void k_gather_vbar(const Seg *segs, const int32_t *loss_seg, const in
 hipError_t launch_adj_group(const AdjArgs &a, int max_inc, hipStream_t s)
 {
     if (a.n_loss == 0 || a.K <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_adj_deliver, dim3((unsigned)a.n_inst, (unsigned)a.K), dim3(256), 8 * (size_t)max_inc, s, a);
+    AdjArgs d = a;
+    for (d.k_first = 0; d.k_first < a.K; d.k_first += kAdjSteps)
+        hipLaunchKernelGGL(k_adj_deliver, dim3((unsigned)a.n_inst, (unsigned)std::min(a.K - d.k_first, kAdjSteps)),
+                           dim3(256), 8 * (size_t)max_inc, s, d);
     const int segs = (a.K + a.seg_steps - 1) / a.seg_steps;
     hipLaunchKernelGGL(k_adj_states, dim3((unsigned)((a.n_loss + kWave - 1) / kWave), (unsigned)segs), dim3(kWave), 0,
                        s, a);

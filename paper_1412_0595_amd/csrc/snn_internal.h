@@ -339,6 +339,7 @@ struct LtpArgs {
 constexpr int kResRing = 16;     // steps of spike words in the exchange ring (a power of two)
 constexpr int kResCheck = 8;     // a block that needs no neuron's words reads them every so many steps
 constexpr int kResNeuronRec = 176, kResSourceRec = 32;   // bytes of a word's constants in LDS
+constexpr int64_t kResLds = 160 * 1024 - 512;   // dynamic LDS of a block at most (it has a few words of its own)
 constexpr int kResList = 1024;   // spiking rows a block lists in LDS for one step
 
 // A projection (or the part of it that ends in one block), as the block's
@@ -451,6 +452,7 @@ struct AdjArgs {
     int32_t K;                   // steps in the group
     int32_t seg_steps;           // steps in a segment (the recording's last may be shorter)
     int64_t first_seg, n_seg;    // the group's first segment, segments of the recording
+    int32_t k_first;             // k_adj_deliver: step of the group that the launch begins at
     const int32_t *rp_pool;
     const int32_t *col_pool;
     const float *w_pool;

@@ -666,12 +666,13 @@ const void *resident_kernel(int feat)
 
 }  // namespace
 
+// (the attribute is the function's, so every network sets the same value)
 bool resident_fits(int feat, int block, size_t lds, int blocks, bool together, int n_cu)
 {
     const void *k = resident_kernel(feat);
     if (!k) return false;
     int per_cu = 0;
-    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResLds) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, block, lds) != hipSuccess) {
         (void)hipGetLastError();
         return false;

@@ -1722,7 +1722,6 @@ static int plan_resident(snn_net *net)
         return SNN_OK;
     }
     const int n_cu = prop.multiProcessorCount;
-    constexpr int64_t kLds = 160 * 1024 - 512;   // (the kernel has a few words of its own)
 
     struct Inst { int64_t w_first, n_words, n_state, n_poi, nnz; double load, read_load; };
     std::vector<Inst> in(net->n_inst);
@@ -1835,14 +1834,17 @@ static int plan_resident(snn_net *net)
             }
             L.blocks += M;
         }
-        const int64_t fit = std::min<int64_t>(kLds / std::max<int64_t>(worst_lds, 1), 4);
+        const int64_t fit = std::min<int64_t>(kResLds / std::max<int64_t>(worst_lds, 1), 4);
         if (fit < 1 || (split && L.blocks > n_cu)) return L.blocks = 0, L;
         // blocks beyond one per CU share it, beyond what fits they follow one another
         L.cost = worst * (double)((L.blocks + n_cu - 1) / n_cu);
         return L;
     };
     Layout best;
-    for (double per = 4.0; best.blocks == 0 && per < 64.0; per *= 1.05) best = lay_out(per);
+    for (double per = net->n_inst > n_cu ? 1e9 : 4.0; best.blocks == 0; per *= 1.05) {
+        best = lay_out(per);
+        if (per > 256.0) break;      // one block per instance, whatever their size
+    }
     if (best.blocks == 0 || best.cost > step_kernels) return SNN_OK;
 
     // ---- the tables
@@ -1945,7 +1947,7 @@ static int plan_resident(snn_net *net)
     }
     R.blocks = (int)best.blocks;
     // slice bounds in LDS as far as they fit, neurons' first
-    const int64_t room = R.blocks > n_cu ? kLds / 2 : kLds;
+    const int64_t room = R.blocks > n_cu ? kResLds / 2 : kResLds;
     for (size_t k = 0; k < blocks.size(); ++k) {
         int64_t used = align_up(best.lds[k], 8), at = 0;
         for (int pass = 0; pass < 2; ++pass)
@@ -1982,8 +1984,14 @@ static int plan_resident(snn_net *net)
     R.d_xbuf = (uint64_t *)dev_alloc(net, 8 * (size_t)std::max<int64_t>(x_total, 1));
     int64_t *d_totals = (int64_t *)dev_alloc(net, 8 * blocks.size());
     if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_sources || !R.d_reads || !R.d_bounds || !R.d_from ||
-        !R.d_syn || !R.d_xbuf || !d_totals)
-        return fail(SNN_ENOMEM, "device allocation failed");
+        !R.d_syn || !R.d_xbuf || !d_totals) {
+        // no room for the tables: the step kernels do without them
+        for (void *p : {(void *)R.d_blocks, (void *)R.d_words, (void *)R.d_feeds, (void *)R.d_wfeeds, (void *)R.d_sources,
+                        (void *)R.d_reads, (void *)R.d_bounds, (void *)R.d_from, (void *)R.d_syn, (void *)R.d_xbuf,
+                        (void *)d_totals})
+            dev_free(net, p);
+        return SNN_OK;
+    }
     for (size_t k = 0; k < feeds.size(); ++k) feeds[k].bounds = R.d_bounds + sources[k].bounds0;
     int rc;
     if ((rc = h2d(net, R.d_blocks, blocks.data(), sizeof(ResBlock) * blocks.size()))) return rc;
@@ -2218,19 +2226,31 @@ static int deliver_queued_to_fused(snn_net *net, int mode)
 
 namespace {
 
-// Lays out the pending deliveries of S(t-1), where its spike words alone
-// hold them, as the current mode's step kernels take them.
+// Weights of the column copies that tile mode pulls from.
+int refresh_pull(snn_net *net)
+{
+    if (!net->pull_stale) return SNN_OK;
+    HIP_OK(launch_gather_weights(net->d_w, net->d_pull_perm, (float *)net->d_pull_w, 4 * kWave * net->pull_count,
+                                 net->stream));
+    net->pull_stale = false;
+    return SNN_OK;
+}
+
+// Before the step kernels run: lays out the pending deliveries of S(t-1),
+// where its spike words alone hold them, as the current mode's kernels take
+// them, and brings the copies that tile mode pulls from up to date.
 int materialize(snn_net *net)
 {
+    int rc;
+    if (net->launch.mode == kModeTiles && (rc = refresh_pull(net))) return rc;
     if (!net->pend_bits) return SNN_OK;
     if (net->pend_delivered) {
         // nothing is pending: empty queues, as the switch out of fused mode left them
-        const int rc = clear_queues(net);
+        rc = clear_queues(net);
         if (!rc) net->pend_bits = false;
         return rc;
     }
-    int rc = clear_queues(net);
-    if (rc) return rc;
+    if ((rc = clear_queues(net))) return rc;
     const int mode = net->launch.mode;
     if (mode == kModeFused) net->launch.mode = kModeRows;
     rc = rebuild_pending(net, -1, nullptr);
@@ -2391,16 +2411,6 @@ int snn_get_launch(const snn_net *net, snn_launch *out)
     return SNN_OK;
 }
 
-// Weights of the column copies that tile mode pulls from.
-static int refresh_pull(snn_net *net)
-{
-    if (!net->pull_stale) return SNN_OK;
-    HIP_OK(launch_gather_weights(net->d_w, net->d_pull_perm, (float *)net->d_pull_w, 4 * kWave * net->pull_count,
-                                 net->stream));
-    net->pull_stale = false;
-    return SNN_OK;
-}
-
 int snn_set_launch(snn_net *net, const snn_launch *in)
 {
     int rc = check_net(net);
@@ -2422,7 +2432,6 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
     const snn_launch prev = net->launch;
     net->launch = *in;
     net->res.on = false;      // a shape given by the caller is the one that runs
-    if (in->mode == kModeTiles && (rc = refresh_pull(net))) return rc;
     if ((rc = update_qbuckets(net))) return rc;
     if (net->pend_bits) {
         if ((rc = materialize(net))) return rc;
@@ -2446,6 +2455,7 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
         rc = rebuild_pending(net, -1, nullptr);
     }
     if (rc) return rc;
+    if ((rc = materialize(net))) return rc;
     drop_graphs(net);
     return SNN_OK;
 }
@@ -2609,7 +2619,7 @@ int snn_set_weights_device(snn_net *net, const float *src)
             return fail(SNN_ERANGE, "projection %zu: g_scale * column sum / (1 - decay) exceeds %g uS", q, kGLimit);
     }
     HIP_OK(hipMemcpyAsync(net->d_w, src, 4 * (size_t)net->w_count, hipMemcpyDeviceToDevice, net->stream));
-    // the copies that the steps use; tile mode's also on a switch to it
+    // the copies that the steps use; tile mode's when its kernels run
     net->pull_stale = true;
     if (net->launch.mode == kModeTiles && !net->res.on && (rc = refresh_pull(net))) return rc;
     if (net->res.on)
@@ -2666,7 +2676,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     // segments per group of the backward pass: as many as kTapeBytes hold, so
     // that their steps run in parallel
     const int64_t per_seg = 8 * std::max<int64_t>(n_loss, 1) * K * (4 + 2 * n_in_max);
-    const int64_t group = std::min(nseg, std::max<int64_t>(1, std::min(kTapeBytes / per_seg, kTapeSteps / K)));
+    int64_t group = std::min(nseg, std::max<int64_t>(1, std::min(kTapeBytes / per_seg, kTapeSteps / K)));
     // (re)allocate the recording, unless the last one had the same shape
     const bool same = net->d_rec_raster && net->rec_pop == pop && net->rec_T == T && net->rec_K == K;
     net->recorded = false;
@@ -2681,10 +2691,17 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
         net->d_loss_base = (int64_t *)dev_alloc(net, 8 * (size_t)(net->n_inst + 1));
         net->d_loss_owner = (int32_t *)dev_alloc(net, 4 * owner.size());
         net->d_gitems = (int4 *)dev_alloc(net, sizeof(int4) * std::max<size_t>(items.size(), 1));
-        const size_t steps = (size_t)(group * K), nl = (size_t)std::max<int64_t>(n_loss, 1);
-        net->d_tape_x = (double *)dev_alloc(net, 8 * steps * 4 * nl);
-        net->d_tape_g = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
-        net->d_lg = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
+        const size_t nl = (size_t)std::max<int64_t>(n_loss, 1);
+        // (one segment's tape if a group's cannot be had)
+        for (;; group = 1) {
+            const size_t steps = (size_t)(group * K);
+            net->d_tape_x = (double *)dev_alloc(net, 8 * steps * 4 * nl);
+            net->d_tape_g = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
+            net->d_lg = (double *)dev_alloc(net, 8 * steps * n_in_max * nl);
+            if ((net->d_tape_x && net->d_tape_g && net->d_lg) || group == 1) break;
+            for (double *p : {net->d_tape_x, net->d_tape_g, net->d_lg}) dev_free(net, p);
+        }
+        net->rec_group = group;
         net->d_lam = (double *)dev_alloc(net, 8 * (size_t)(4 + n_in_max) * nl);
         if (!net->d_ckpt_state || !net->d_ckpt_G || !net->d_loss_seg || !net->d_loss_base || !net->d_loss_owner ||
             !net->d_gitems || !net->d_tape_x || !net->d_tape_g || !net->d_lg || !net->d_lam)
@@ -2699,7 +2716,6 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     net->n_loss = n_loss;
     net->n_in_max = n_in_max;
     net->max_inc = max_inc;
-    net->rec_group = group;
     net->n_gitems = (int64_t)items.size();
     net->rec_pop = pop;
     net->rec_T = T;
@@ -2713,6 +2729,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     na.raster_steps = (int32_t)T;
     const PropArgs pa = prop_args(net);
     const bool resident = use_resident(net, T);
+    if (!resident && (rc = materialize(net))) return rc;
     for (int64_t t = 0; t < T; ++t) {
         if (t % K == 0) {
             const int64_t sgi = t / K;

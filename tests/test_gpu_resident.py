@@ -138,3 +138,78 @@ def test_recorded_steps(snn):
         got.append(run(net))
         net.close()
     assert not differing(*got)
+
+
+def test_several_networks_step_at_once(snn):
+    """Networks on streams and threads of their own, whose blocks together
+    are more than the device holds at once."""
+    import threading
+
+    import torch
+    print("case: resident networks at once", flush=True)
+    specs = [layered(1, 300, 5000 + 501 * i, 257) for i in range(4)]
+
+    def run(net, k):
+        for _ in range(5):
+            net.step(60)
+        net.sync()
+        got[k] = everything(net, specs[k])
+    ref = []
+    for spec in specs:
+        net = snn.Network(spec)
+        net.set_launch(mode=0)
+        net.step(300)
+        ref.append(everything(net, spec))
+        net.close()
+    got = {}
+    nets = [snn.Network(spec, stream=torch.cuda.Stream()) for spec in specs]
+    threads = [threading.Thread(target=run, args=(net, k)) for k, net in enumerate(nets)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, net in enumerate(nets):
+        assert not differing(ref[k], got[k]), k
+        net.close()
+
+
+def test_weights_set_while_tile_mode_waits(snn):
+    """Weights set while the steps run resident reach the copies of the mode
+    chosen afterwards."""
+    import torch
+    print("case: resident then tiles", flush=True)
+    spec = layered(1, 100, 700, 65)
+    out = []
+    for first in (None, dict(mode=1)):
+        net = snn.Network(spec)
+        if first:
+            net.set_launch(**first)
+        w = torch.empty(net.weight_count, dtype=torch.float32, device="cuda")
+        net.get_weights_device(w)
+        net.step(30)
+        net.set_weights_device(w * 0.5)
+        net.step(30)
+        net.set_launch(mode=1)
+        for p in range(3):
+            net.set_last_spikes(0, p, np.ones(spec["instances"][0]["pops"][p]["n"], np.uint8))
+        net.step(1)
+        net.step(30)
+        out.append(everything(net, spec))
+        net.close()
+    assert not differing(*out)
+
+
+def test_long_segments_and_groups(snn):
+    """The gradient does not depend on how many segments the tape holds: the
+    no-allocation entry point's smaller one, and one segment of all steps."""
+    import torch
+    print("case: adjoint groups", flush=True)
+    spec = layered(2, 60, 300, 40)
+    for T, K in ((64, 1), (150, 40), (120, 120)):
+        net = snn.Network(spec, record_vbar=("C",))
+        vb = net.forward_record(2, T, K)
+        dg, ds, bad = net.backward(vb, check=True)
+        dg2, ds2 = torch.empty_like(dg), torch.empty_like(ds)
+        net.backward_noalloc(vb, dg2, ds2)
+        assert bad == 0 and torch.equal(dg, dg2) and float(dg.abs().sum()) > 0
+        net.close()
