@@ -378,9 +378,21 @@ struct ResBlock {
     int32_t n_early, n_late; // sources' that feed it; all with a membrane
     int32_t late_feeds;      // 1: some of the latter feed it
     int32_t pad_;
+    int64_t early0;          // place in drawn_at
     int64_t syn0;            // the block's synapses
     int64_t x_off;           // the instance's exchange ring
 };
+
+// Sources drawn ahead of a launch: 64 sources of one stream, and the words of
+// the network that they are.
+struct ResDraw {
+    uint32_t seed_lo, seed_hi, pop;
+    int32_t j0, active;      // first source, sources
+    int32_t alias0, n_alias;
+    int32_t pad_;
+    uint64_t thresh;
+};
+constexpr int kResDrawSteps = 16;   // steps drawn by one wavefront
 
 struct ResArgs {
     const Seg *segs;
@@ -407,6 +419,9 @@ struct ResArgs {
     StepState *st;
     int64_t t0, n;
     uint32_t tag0;           // exchange tag of step t0
+    const uint64_t *drawn;   // the launch's sources: [step][n_drawn][2] of (tag, half word), or null (the
+    int64_t n_drawn;         // blocks draw and exchange them)
+    const uint32_t *drawn_at;   // per block and early word: place among the n_drawn
     int32_t skip_first;      // 1: S(t0 - 1) is already in the conductances
     int64_t ckpt_every;      // > 0: the state at the start of every step k * ckpt_every < ckpt_end that
     int64_t ckpt_end;        // a step of the launch ends at goes to checkpoint k
@@ -420,6 +435,10 @@ hipError_t launch_resident_bounds(const ResBlock *blocks, int n, const ResSource
                                   const int32_t *col_pool, int32_t *bounds, int32_t *from, int64_t *totals, hipStream_t s);
 hipError_t launch_resident_fill(const ResBlock *blocks, int n, const ResSource *srcs, const int32_t *col_pool,
                                 const float *w_pool, const int32_t *bounds, const int32_t *from, int2 *syn, hipStream_t s);
+// Draws the sources of the launch `a` (a.drawn is written).
+hipError_t launch_resident_draw(const ResArgs &a, const ResDraw *draws, const int32_t *alias, hipStream_t s);
+// After the launch: their spike words of its last step.
+hipError_t launch_resident_last(const ResArgs &a, const ResDraw *draws, const int32_t *alias, hipStream_t s);
 // Whether the kernel runs with this block size and LDS, and (together) all
 // blocks are resident at once.
 bool resident_fits(int feat, int block, size_t lds, int blocks, bool together, int n_cu);

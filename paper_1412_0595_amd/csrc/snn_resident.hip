@@ -15,12 +15,16 @@
 // is what this kernel shortens: spike words, a list of the spiking rows in LDS
 // (so that the waves share them evenly), synapses (a block's own, slice after
 // slice; their bounds in LDS where these fit), LDS sums, voltage.  A step's
-// last voltage needs the
-// rates of all substeps but the first, whose gates and ionic current the
-// step's input does not enter, and the last, whose gates only the next step
-// uses: of three substeps' rates one lies before the spike words and two run
-// after they have left, while they travel.  Waves without a neuron draw the
-// sources and poll the words meanwhile.
+// last voltage needs the rates of all substeps but the first, whose gates and
+// ionic current the step's input does not enter, and the last, whose gates
+// only the next step uses: of three substeps' rates one lies before the spike
+// words and two run after they have left, while they travel.  Waves without a
+// neuron draw the sources (in short calls) and poll the words meanwhile.
+//
+// Time per step, step kernels -> here (2 000 steps a call): 1 100 neurons in 7
+// blocks 7.0 -> 3.2 us, 21 000 neurons in 96 blocks 10.1 -> 4.4, 325 networks of
+// 220 neurons 19.7 -> 5.0, 48 of 2 000 to 20 000 neurons 37 -> 18.  An
+// exchange takes 0.8 to 2 of these, one evaluation of the rates 0.6.
 #include <algorithm>
 
 #include "snn_device.h"
@@ -31,6 +35,7 @@ namespace {
 
 using CResBlock = const __attribute__((address_space(4))) ResBlock;
 
+using GlobalU64 = __attribute__((address_space(1))) uint64_t;
 using GlobalI32 = __attribute__((address_space(1))) int32_t;   // (generic loads would wait for LDS and memory alike)
 
 constexpr int kResPoll = 4;    // half words a lane asks for at once
@@ -147,13 +152,15 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     const int64_t w_first = B.w_first;      // the instance's first spike word
     const bool multi = B.n_blocks > 1;
     const bool late_feeds = B.late_feeds != 0;
+    const bool drawn = a.drawn != nullptr;
     const double s_fix = (double)a.gscale[B.inst] * kFixOne;
     const int2 *syn = a.syn + B.syn0;
     uint64_t *xw = a.xbuf + B.x_off;        // kResRing slots of 2 n_words tagged halves
 
     // LDS: conductances, neuron state, recorded sums, feeds, the words'
     // constants, spike words of two steps, the words that the block reads
-    // (sources' first), each word's feeds, the listed rows (neurons of the
+    // (sources' first) and the latters' places among the drawn, each word's
+    // feeds, the listed rows (neurons of the
     // instance), slice bounds of the feeds that have them here
     unsigned long long *s_g = reinterpret_cast<unsigned long long *>(s_mem);
     double *s_state = reinterpret_cast<double *>(s_g + n_g);
@@ -163,7 +170,8 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     SourceRec *s_src_rec = reinterpret_cast<SourceRec *>(s_rec + n_state);
     uint64_t *s_word = reinterpret_cast<uint64_t *>(s_src_rec + n_poi);
     uint32_t *s_read = reinterpret_cast<uint32_t *>(s_word + 2 * n_words);
-    uint32_t *s_wfeed = s_read + n_read;
+    uint32_t *s_drawn = s_read + n_read;
+    uint32_t *s_wfeed = s_drawn + n_early;
     uint32_t *s_list = s_wfeed + n_words;
     int32_t *s_bounds = reinterpret_cast<int32_t *>(s_list + kResList);
 
@@ -172,6 +180,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     for (int i = threadIdx.x; i < B.n_feed; i += nt) s_feed[i] = a.feeds[B.feed0 + i];
     for (int i = threadIdx.x; i < n_words; i += nt) s_wfeed[i] = a.wfeeds[B.wfeed0 + i];
     for (int i = threadIdx.x; i < n_read; i += nt) s_read[i] = a.reads[B.read0 + i];
+    for (int i = threadIdx.x; i < n_early; i += nt) s_drawn[i] = a.drawn_at[B.early0 + i];
     for (int w = threadIdx.x; w < n_state + n_poi; w += nt) {
         const ResWord &W = a.words[B.word0 + w];
         const Seg &S = a.segs[W.seg];
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     // The block's Poisson words of step t, two at a time by the next free wave
     // (one draw's dependent products hide behind the other's).
     auto sources = [&](int64_t t) __attribute__((always_inline)) {
-        while (n_poi > 0) {
+        while (n_poi > 0 && !drawn) {
             int w = 0;
             if (lane == 0) w = (int)atomicAdd(&s_src[t & 1], 2u);
             w = __builtin_amdgcn_readfirstlane(w);
@@ -272,7 +281,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
             asm volatile("");
             return;
         }
-        if (!multi) {
+        if (!multi && !drawn) {
             const uint32_t *src = reinterpret_cast<const uint32_t *>(s_word + (t & 1) * n_words);
 #pragma unroll
             for (int u = 0; u < kResPoll; ++u) {
@@ -289,17 +298,19 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
         const uint32_t tag = a.tag0 + (uint32_t)(t - t0);
         const uint64_t *src = xw + (t & (kResRing - 1)) * 2 * n_words;
         const int64_t since = wall_clock64();
-        uint32_t at[kResPoll];
+        const GlobalU64 *at[kResPoll];
 #pragma unroll
         for (int u = 0; u < kResPoll; ++u) {
             const int i = min(i0 + u * kWave + lane, end - 1);
-            at[u] = 2 * s_read[i >> 1] + (i & 1);
+            at[u] = (const GlobalU64 *)src + 2 * s_read[i >> 1] + (i & 1);
+            if (drawn && i < 2 * n_early)
+                at[u] = (const GlobalU64 *)a.drawn + ((t - t0) * a.n_drawn + s_drawn[i >> 1]) * 2 + (i & 1);
         }
         for (uint32_t tries = 1;; ++tries) {
             uint64_t x[kResPoll];
 #pragma unroll
             for (int u = 0; u < kResPoll; ++u)
-                if (i0 + u * kWave < end) x[u] = __hip_atomic_load(src + at[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (i0 + u * kWave < end) x[u] = __hip_atomic_load(at[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             bool here = true;
 #pragma unroll
             for (int u = 0; u < kResPoll; ++u) {
@@ -648,6 +659,69 @@ hipError_t launch_resident_fill(const ResBlock *blocks, int n, const ResSource *
     const int y = std::max(1, std::min(256, 4096 / n));
     hipLaunchKernelGGL(k_resident_fill, dim3((unsigned)n, (unsigned)y), dim3(256), 0, s, blocks, srcs, col_pool, w_pool,
                        bounds, from, syn);
+    return hipGetLastError();
+}
+
+// The sources of a launch, before it: streams that several instances share
+// (the runs of a sweep) are drawn once, all steps side by side; inside the
+// launch each block would draw its own, step by step, beside its neurons (a
+// sweep of 125 networks with 500 to 5 000 sources: 8.9 us a step, 7.0 with
+// the draws ahead; 325 small ones 6.1 and 5.6).  A wavefront per word and
+// kResDrawSteps steps.
+__global__ __launch_bounds__(256) void k_resident_draw(ResArgs a, const ResDraw *draws, const int32_t *alias)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t d = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (d >= a.n_drawn) return;
+    const ResDraw &D = draws[d];
+    uint64_t *out = const_cast<uint64_t *>(a.drawn);
+    const int64_t k0 = (int64_t)blockIdx.y * kResDrawSteps, k1 = min(k0 + kResDrawSteps, a.n);
+    const uint32_t seed_lo = D.seed_lo, seed_hi = D.seed_hi, pop = D.pop, j = (uint32_t)(D.j0 + lane);
+    const uint64_t thresh = D.thresh;
+    const bool active = lane < D.active;
+    int32_t count = 0;
+    for (int64_t k = k0; k < k1; ++k) {
+        const int64_t t = a.t0 + k;
+        const bool spike = active && (uint64_t)philox_first_word(j, (uint32_t)t, (uint32_t)((uint64_t)t >> 32), pop, seed_lo,
+                                                                 seed_hi) < thresh;
+        const uint64_t ball = __ballot(spike);
+        count += spike ? 1 : 0;
+        if (lane < 2)
+            out[(k * a.n_drawn + d) * 2 + lane] =
+                (uint64_t)(uint32_t)(a.tag0 + (uint32_t)k) << 32 | (uint32_t)(ball >> (32 * lane));
+        // (of a ring shorter than the launch, its last round)
+        if (a.raster && k >= a.n - a.raster_steps)
+            for (int i = lane; i < D.n_alias; i += kWave)
+                a.raster[(t % a.raster_steps) * a.n_waves + alias[D.alias0 + i]] = ball;
+    }
+    if (count)
+        for (int i = 0; i < D.n_alias; ++i) atomicAdd(&a.counts[(int64_t)alias[D.alias0 + i] * kWave + lane], count);
+}
+
+// Their spike words of the launch's last step, after it (before, the slot may
+// hold the words that its first step delivers).
+__global__ void k_resident_last(ResArgs a, const ResDraw *draws, const int32_t *alias)
+{
+    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= a.n_drawn) return;
+    const uint64_t *w = a.drawn + ((a.n - 1) * a.n_drawn + d) * 2;
+    const uint64_t ball = (uint64_t)(uint32_t)w[0] | w[1] << 32;
+    const ResDraw &D = draws[d];
+    for (int i = 0; i < D.n_alias; ++i) a.bits[((a.t0 + a.n - 1) & 1) * a.n_waves + alias[D.alias0 + i]] = ball;
+}
+
+hipError_t launch_resident_last(const ResArgs &a, const ResDraw *draws, const int32_t *alias, hipStream_t s)
+{
+    if (a.n_drawn == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_resident_last, dim3((unsigned)((a.n_drawn + 63) / 64)), dim3(64), 0, s, a, draws, alias);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_draw(const ResArgs &a, const ResDraw *draws, const int32_t *alias, hipStream_t s)
+{
+    if (a.n_drawn == 0) return hipSuccess;
+    const dim3 grid((unsigned)((a.n_drawn + 3) / 4), (unsigned)((a.n + kResDrawSteps - 1) / kResDrawSteps));
+    hipLaunchKernelGGL(k_resident_draw, grid, dim3(256), 0, s, a, draws, alias);
     return hipGetLastError();
 }
 

@@ -8,8 +8,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/snn.h"
@@ -145,6 +147,11 @@ struct ResidentPlan {
     ResWord *d_words;
     ResFeed *d_feeds;
     ResSource *d_sources;
+    ResDraw *d_draws;        // the distinct words of sources, and
+    int32_t *d_alias;        // the words of the network that each is
+    uint32_t *d_drawn_at;
+    uint64_t *d_drawn;       // drawn_steps steps of them
+    int64_t n_drawn, drawn_steps;
     uint32_t *d_wfeeds, *d_reads;
     int32_t *d_bounds, *d_from;
     int2 *d_syn;
@@ -534,6 +541,8 @@ constexpr int64_t kTapeBytes = (int64_t)512 << 20, kTapeSteps = 32768;
 
 constexpr int64_t kResidentMin = 8;        // steps in a call that are worth a cooperative launch
 constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
+constexpr int64_t kResidentDraw = 32;      // steps in a call whose sources are drawn ahead
+constexpr int64_t kDrawnBytes = (int64_t)64 << 20, kDrawnSteps = 2048;   // of them in a launch, at most
 
 // Whether a call of n steps runs resident.  A cooperative launch costs more
 // than the graph replay of a few steps, but less than laying out the pending
@@ -597,13 +606,20 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     a.ckpt_state = net->d_ckpt_state;
     a.ckpt_G = net->d_ckpt_G;
     a.g_stride = std::max<int64_t>(net->G_count, 1);
+    // sources drawn ahead, but for calls of a few steps (a launch more)
+    const bool draw = n >= kResidentDraw && net->res.d_drawn;
+    a.n_drawn = net->res.n_drawn;
+    a.drawn_at = net->res.d_drawn_at;
     while (n > 0) {
         a.t0 = net->t;
-        a.n = std::min(n, kResidentLaunch);
+        a.n = std::min(n, draw ? net->res.drawn_steps : kResidentLaunch);
         a.tag0 = net->res.tag;
         a.skip_first = net->pend_delivered ? 1 : 0;
+        a.drawn = draw ? net->res.d_drawn : nullptr;
+        if (draw) HIP_OK(launch_resident_draw(a, net->res.d_draws, net->res.d_alias, net->stream));
         HIP_OK(launch_resident(a, na.feat, net->res.blocks, net->res.block, net->res.lds, net->res.together,
                                net->stream));
+        if (draw) HIP_OK(launch_resident_last(a, net->res.d_draws, net->res.d_alias, net->stream));
         net->res.tag += (uint32_t)a.n;
         net->pend_delivered = false;
         net->t += a.n;
@@ -1828,7 +1844,7 @@ static int plan_resident(snn_net *net)
                 L.state.push_back(st[r]);
                 L.poi.push_back(po[r]);
                 L.lds.push_back(8 * g[r] + (kResNeuronRec + 2560 + ((feat & kFeatRec) ? 512 : 0)) * st[r] +
-                                kResSourceRec * po[r] + 24 * I.n_words + 4 * kResList + (int64_t)sizeof(ResFeed) * feeds[r]);
+                                kResSourceRec * po[r] + 28 * I.n_words + 4 * kResList + (int64_t)sizeof(ResFeed) * feeds[r]);
                 worst_lds = std::max(worst_lds, L.lds.back());
                 worst = std::max(worst, 2.0 + 4.0 * std::ceil((double)st[r] / 16.0));
             }
@@ -1853,7 +1869,32 @@ static int plan_resident(snn_net *net)
     std::vector<ResFeed> feeds;
     std::vector<ResSource> sources;
     std::vector<uint32_t> wfeeds;
-    std::vector<uint32_t> reads;
+    std::vector<uint32_t> reads, drawn_at;
+    // distinct source populations: same stream, same size
+    std::vector<ResDraw> draws;
+    std::vector<std::vector<int32_t>> draw_alias;
+    std::vector<int64_t> seg_draw(net->segs.size(), -1);   // its first word among the draws
+    std::map<std::tuple<uint64_t, int32_t, int32_t, uint64_t>, int64_t> streams;
+    for (size_t sg = 0; sg < net->segs.size(); ++sg) {
+        const Seg &S = net->segs[sg];
+        if (S.kind != kPoisson) continue;
+        const auto at = streams.emplace(std::make_tuple(S.seed, S.pop, S.n, S.thresh), (int64_t)draws.size());
+        seg_draw[sg] = at.first->second;
+        for (int64_t w = 0; w < align_up(S.n, kWave) / kWave; ++w) {
+            if (at.second) {
+                draws.push_back(ResDraw{(uint32_t)S.seed, (uint32_t)(S.seed >> 32), (uint32_t)S.pop, (int32_t)(w * kWave),
+                                        (int32_t)std::min<int64_t>(kWave, S.n - w * kWave), 0, 0, 0, S.thresh});
+                draw_alias.emplace_back();
+            }
+            draw_alias[seg_draw[sg] + w].push_back((int32_t)(S.base / kWave + w));
+        }
+    }
+    std::vector<int32_t> alias;
+    for (size_t k = 0; k < draws.size(); ++k) {
+        draws[k].alias0 = (int32_t)alias.size();
+        draws[k].n_alias = (int32_t)draw_alias[k].size();
+        alias.insert(alias.end(), draw_alias[k].begin(), draw_alias[k].end());
+    }
     int64_t x_total = 0, bounds_total = 0, syn_total = 0, max_lds = 0;
     for (int b = 0; b < net->n_inst; ++b) {
         const Inst &I = in[b];
@@ -1868,6 +1909,7 @@ static int plan_resident(snn_net *net)
             B.wfeed0 = (int64_t)wfeeds.size();
             B.feed0 = (int64_t)feeds.size();
             B.read0 = (int64_t)reads.size();
+            B.early0 = (int64_t)drawn_at.size();
             B.x_off = x_total;
             std::vector<int> pre;                         // pre population of each of its feeds
             for (int pass = 0; pass < 2; ++pass)          // words with a membrane first
@@ -1937,6 +1979,7 @@ static int plan_resident(snn_net *net)
                         const int64_t rel = S.base / kWave - I.w_first + w;
                         if (pass == 0 && wfeeds[B.wfeed0 + rel] == 0) continue;
                         reads.push_back((uint32_t)rel);
+                        if (pass == 0) drawn_at.push_back((uint32_t)(seg_draw[sg] + w));
                         (pass == 0 ? B.n_early : B.n_late)++;
                     }
                 }
@@ -1983,12 +2026,19 @@ static int plan_resident(snn_net *net)
     R.d_syn = (int2 *)dev_alloc(net, sizeof(int2) * (size_t)std::max<int64_t>(net->w_count, 1));
     R.d_xbuf = (uint64_t *)dev_alloc(net, 8 * (size_t)std::max<int64_t>(x_total, 1));
     int64_t *d_totals = (int64_t *)dev_alloc(net, 8 * blocks.size());
+    R.n_drawn = (int64_t)draws.size();
+    R.drawn_steps = std::min(kDrawnSteps, kDrawnBytes / (16 * std::max<int64_t>(R.n_drawn, 1)));
+    R.d_draws = (ResDraw *)dev_alloc(net, sizeof(ResDraw) * std::max<size_t>(draws.size(), 1));
+    R.d_alias = (int32_t *)dev_alloc(net, 4 * std::max<size_t>(alias.size(), 1));
+    R.d_drawn_at = (uint32_t *)dev_alloc(net, 4 * std::max<size_t>(drawn_at.size(), 1));
+    if (R.n_drawn > 0 && R.drawn_steps >= kResidentDraw)
+        R.d_drawn = (uint64_t *)dev_alloc(net, 16 * (size_t)(R.n_drawn * R.drawn_steps));   // (null: drawn in the launch)
     if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_sources || !R.d_reads || !R.d_bounds || !R.d_from ||
-        !R.d_syn || !R.d_xbuf || !d_totals) {
+        !R.d_syn || !R.d_xbuf || !d_totals || !R.d_draws || !R.d_alias || !R.d_drawn_at) {
         // no room for the tables: the step kernels do without them
         for (void *p : {(void *)R.d_blocks, (void *)R.d_words, (void *)R.d_feeds, (void *)R.d_wfeeds, (void *)R.d_sources,
                         (void *)R.d_reads, (void *)R.d_bounds, (void *)R.d_from, (void *)R.d_syn, (void *)R.d_xbuf,
-                        (void *)d_totals})
+                        (void *)d_totals, (void *)R.d_draws, (void *)R.d_alias, (void *)R.d_drawn_at, (void *)R.d_drawn})
             dev_free(net, p);
         return SNN_OK;
     }
@@ -2000,6 +2050,9 @@ static int plan_resident(snn_net *net)
     if ((rc = h2d(net, R.d_sources, sources.data(), sizeof(ResSource) * sources.size()))) return rc;
     if ((rc = h2d(net, R.d_wfeeds, wfeeds.data(), 4 * wfeeds.size()))) return rc;
     if ((rc = h2d(net, R.d_reads, reads.data(), 4 * reads.size()))) return rc;
+    if ((rc = h2d(net, R.d_draws, draws.data(), sizeof(ResDraw) * draws.size()))) return rc;
+    if ((rc = h2d(net, R.d_alias, alias.data(), 4 * alias.size()))) return rc;
+    if ((rc = h2d(net, R.d_drawn_at, drawn_at.data(), 4 * drawn_at.size()))) return rc;
     HIP_OK(launch_fill_zero(R.d_xbuf, 8 * (size_t)std::max<int64_t>(x_total, 1), net->stream));
     HIP_OK(launch_resident_bounds(R.d_blocks, R.blocks, R.d_sources, net->d_rp, net->d_col, R.d_bounds, R.d_from, d_totals,
                                   net->stream));

@@ -140,6 +140,31 @@ def test_recorded_steps(snn):
     assert not differing(*got)
 
 
+def test_sources_drawn_ahead(snn):
+    """Streams that instances share or not, over calls above and below the
+    length from which sources are drawn ahead, longer and shorter than the
+    raster ring, and a rate at which every source spikes."""
+    print("case: resident sources", flush=True)
+    shared = layered(1, 130, 300, 20)["instances"][0]
+    other = dict(shared, seed=77, pops=[dict(shared["pops"][0], rate_hz=900.0), *shared["pops"][1:]])
+    always = dict(shared, pops=[dict(shared["pops"][0], rate_hz=1e5), *shared["pops"][1:]])
+    spec = dict(dt=0.1, substeps=3, instances=[shared, other, dict(shared, g_scale=0.5), always, shared])
+    got = []
+    for mode in (None, dict(mode=0)):
+        net = snn.Network(spec, raster_steps=16)
+        if mode:
+            net.set_launch(**mode)
+        out = []
+        for n in (40, 3, 33, 32, 31, 2100):
+            net.step(n)
+            for b in range(5):
+                out += net.raster(b, 0, net.t - min(n, 16), net.t)
+            out += everything(net, spec)
+        got.append(out)
+        net.close()
+    assert not differing(*got)
+
+
 def test_several_networks_step_at_once(snn):
     """Networks on streams and threads of their own, whose blocks together
     are more than the device holds at once."""
