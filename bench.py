@@ -711,7 +711,8 @@ def step_bench(args):
                    "timed_steps_start_at": t_start,
                    "untimed_before_timed": "pre-roll (leaves the rest transient), warmup, and one run of the "
                                            "timed length that captures the replayed graphs",
-                   "timed_region": "captured hipGraphs of whole steps (64-step graphs and one of the remainder)"},
+                   "timed_region": "captured hipGraphs of whole steps (64-step graphs and one of the remainder); "
+                                   "resident launches of many steps for a network that fits"},
         "synaptic_events_per_s": events_s,
         "spikes": spikes,
         "nan_neurons_total": nan_total,

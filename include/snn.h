@@ -215,7 +215,9 @@ int snn_create(const snn_config *cfg, snn_net **out);
 /* Release every device buffer.  NULL is ignored. */
 void snn_destroy(snn_net *net);
 
-/* Enqueue n_steps timesteps on the net's stream and return (asynchronous):
+/* Enqueue n_steps timesteps on the net's stream and return (asynchronous; a
+ * network whose state fits in LDS and that has no plastic projection steps
+ * many times per launch, until snn_set_launch asks for the step kernels):
  * the per-timestep update of Section 2 (Hodgkin-Huxley neurons integrated
  * at discrete time steps) with spike propagation through the CRS arrays of
  * Section 3.  Each step t: (1) deliver the spikes of step t-1 through every projection
@@ -303,7 +305,8 @@ int snn_get_weights(snn_net *net, int32_t inst, int32_t proj, float *out);
  * n_pre + 1 entries (host int64[total projections, instance-major]). */
 int snn_memory_bytes(const snn_net *net, int64_t *per_proj_bytes);
 
-/* Current / new launch shape; snn_set_launch validates the ranges above
+/* Current / new launch shape of the step kernels, which run from a
+ * snn_set_launch on; snn_set_launch validates the ranges above
  * (SNN_EINVAL, also for mode 2 on a network with plastic projections and for
  * mode 3 with prop_block above 512; the launch is then left as it was).  A
  * change of mode converts the work pending for the next step (delivers it
