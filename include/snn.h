@@ -217,7 +217,9 @@ void snn_destroy(snn_net *net);
 
 /* Enqueue n_steps timesteps on the net's stream and return (asynchronous; a
  * network whose state fits in LDS and that has no plastic projection steps
- * many times per launch, until snn_set_launch asks for the step kernels):
+ * many times per launch, until snn_set_launch asks for the step kernels).  A
+ * stream capture does not record the steps: they run at once, or are refused
+ * (SNN_EINVAL) after steps that ran many to a launch.  One step is
  * the per-timestep update of Section 2 (Hodgkin-Huxley neurons integrated
  * at discrete time steps) with spike propagation through the CRS arrays of
  * Section 3.  Each step t: (1) deliver the spikes of step t-1 through every projection

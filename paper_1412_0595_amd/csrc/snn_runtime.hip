@@ -544,6 +544,16 @@ constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
 constexpr int64_t kResidentDraw = 32;      // steps in a call whose sources are drawn ahead
 constexpr int64_t kDrawnBytes = (int64_t)64 << 20, kDrawnSteps = 2048;   // of them in a launch, at most
 
+bool capturing(const snn_net *net)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(net->stream, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
 // Whether a call of n steps runs resident.  A cooperative launch costs more
 // than the graph replay of a few steps, but less than laying out the pending
 // work again.
@@ -551,12 +561,7 @@ bool use_resident(snn_net *net, int64_t n)
 {
     if (!net->res.on || n < 1) return false;
     if (net->res.together && n < kResidentMin && !net->pend_bits) return false;
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(net->stream, &c) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return c == hipStreamCaptureStatusNone;
+    return !capturing(net);
 }
 
 // The pending deliveries are from here on those of the spike words of
@@ -634,6 +639,11 @@ int run_steps(snn_net *net, int64_t n)
 {
     if (use_resident(net, n))
         return run_resident(net, n, net->raster_steps > 0 ? net->raster : nullptr, std::max(net->raster_steps, 1));
+    // (laying the pending work out reads the spike words back, which would
+    // break the capture and leave the net unusable; the copies that tile mode
+    // pulls from would be brought up to date at the replay only)
+    if (n > 0 && (net->pend_bits || (net->launch.mode == kModeTiles && net->pull_stale)) && capturing(net))
+        return fail(SNN_EINVAL, "the stream is being captured while work for the next step is still to be laid out");
     int rc = n > 0 ? materialize(net) : SNN_OK;
     if (!rc) rc = prepare_graphs(net, n);
     if (rc) return rc;

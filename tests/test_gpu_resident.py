@@ -238,3 +238,34 @@ def test_long_segments_and_groups(snn):
         net.backward_noalloc(vb, dg2, ds2)
         assert bad == 0 and torch.equal(dg, dg2) and float(dg.abs().sum()) > 0
         net.close()
+
+
+@pytest.mark.parametrize("before", (0, 64))
+def test_steps_while_the_stream_is_captured(snn, before):
+    """A capture does not record steps: they run at once or, after resident
+    steps, are refused, and the net goes on as if they had not been asked for."""
+    import torch
+    print("case: capture", before, flush=True)
+    spec = layered(1, 100, 500, 50)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        net, ref = (snn.Network(spec, stream=stream) for _ in range(2))
+        for q in (net, ref):
+            q.step(before)
+            q.sync()
+        graph = torch.cuda.CUDAGraph()
+        refused = False
+        with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+            try:
+                net.step(2)
+            except snn.SNNError as e:
+                refused = True
+                assert e.code == snn.SNN_EINVAL
+        assert refused == (before > 0)
+        if not refused:
+            ref.step(2)
+        for q in (net, ref):
+            q.step(40)
+        assert not differing(everything(net, spec), everything(ref, spec))
+        net.close()
+        ref.close()
