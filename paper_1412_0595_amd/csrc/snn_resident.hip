@@ -555,10 +555,15 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
         if (t + 1 == next_ckpt) next_ckpt += a.ckpt_every;
         if (t + 1 == t_end) break;
 
-        // ---- the next step's sources; deliver S(t)
+        // ---- the next step's sources; deliver S(t).  An even number of steps
+        // leaves its last words in the slot of `bits` that its first step was
+        // delivered from, so no block publishes them before its whole cluster
+        // has read that slot: all await the first step's words of every block
+        // with neurons, whether they need them or not.  (A launch of two steps
+        // would draw its last sources before that; clusters get none.)
         sources(t + 1);
         if (help_i >= 0) {
-            const bool all = t < t0 || (multi && (late_feeds || (t & (kResCheck - 1)) == 0));
+            const bool all = t < t0 || (multi && (late_feeds || t == t0 || (t & (kResCheck - 1)) == 0));
             list_rows(t, all ? r_begin : e_begin, all ? r_end : e_end);
         }
         __syncthreads();

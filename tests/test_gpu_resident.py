@@ -269,3 +269,36 @@ def test_steps_while_the_stream_is_captured(snn, before):
         assert not differing(everything(net, spec), everything(ref, spec))
         net.close()
         ref.close()
+
+
+@pytest.mark.parametrize("name", ["uneven", "wide"])
+def test_even_calls_keep_the_words_they_begin_with(snn, name):
+    """Calls of an even number of steps end in the slot of spike words that
+    they begin from.  "wide" has blocks that begin late (bounds of 20 000 rows
+    to load) beside blocks that only sources feed.  Calls of 2 to 8 steps at
+    every phase of the exchange, and as the last launch of a long call."""
+    print(f"case: resident even calls {name}", flush=True)
+    rng = np.random.default_rng(12)
+    spec = NETS["uneven"]() if name == "uneven" else dict(dt=0.1, substeps=3, instances=[
+        netgen.layered_instance(rng, 1000, 20000, 1000, rate_hz=40.0, p_ab=0.2, p_bc=0.5, seed=12)])
+    flags = [[(rng.random(p["n"]) < 0.05).astype(np.uint8) for p in spec["instances"][0]["pops"]] for _ in range(4)]
+    got = []
+    for mode in (None, dict(mode=0)):
+        net = snn.Network(spec)
+        if mode:
+            net.set_launch(**mode)
+        out = []
+        net.step(64)
+        for n in (2, 4, 6, 8):
+            for phase in range(8):
+                net.step(n)
+                net.step(n)
+                net.step(9 + (phase - net.t) % 8)        # the next calls begin at step phase + 1 mod 8
+                if phase % 2:
+                    for p, f in enumerate(flags[n // 2 - 1]):
+                        net.set_last_spikes(0, p, f)
+            net.step(2048 + n)
+            out += everything(net, spec)
+        got.append(out)
+        net.close()
+    assert not differing(*got)
