@@ -241,7 +241,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
         }
         if (lane == 0) {
             if (a.raster) a.raster[(t % a.raster_steps) * a.n_waves + w_first + rel] = ball;
-            if (t == t_end - 1) a.bits[(t & 1) * a.n_waves + w_first + rel] = ball;
+            if (t == t_end - 1 && (list || !multi)) a.bits[(t & 1) * a.n_waves + w_first + rel] = ball;
         }
     };
     // The block's Poisson words of step t, two at a time by the next free wave
@@ -557,10 +557,10 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
 
         // ---- the next step's sources; deliver S(t).  An even number of steps
         // leaves its last words in the slot of `bits` that its first step was
-        // delivered from, so no block publishes them before its whole cluster
-        // has read that slot: all await the first step's words of every block
-        // with neurons, whether they need them or not.  (A launch of two steps
-        // would draw its last sources before that; clusters get none.)
+        // delivered from, so no block writes them before its whole cluster has
+        // read that slot: all await the first step's words of every block with
+        // neurons, whether they need them or not, and sources, which are drawn
+        // a step ahead, go there after the last step.
         sources(t + 1);
         if (help_i >= 0) {
             const bool all = t < t0 || (multi && (late_feeds || t == t0 || (t & (kResCheck - 1)) == 0));
@@ -575,6 +575,14 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
         }
     }
 
+    // the last step's source words, as this block sent them
+    for (int w = multi && !drawn ? wid : n_poi; w < n_poi; w += nw) {
+        const int rel = s_src_rec[w].rel;
+        const uint64_t *x = xw + ((t_end - 1) & (kResRing - 1)) * 2 * n_words + 2 * rel;
+        if (lane < 2)
+            reinterpret_cast<uint32_t *>(a.bits + ((t_end - 1) & 1) * a.n_waves + w_first + rel)[lane] =
+                (uint32_t)__hip_atomic_load(x + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.st->t_prop = t_end;
         a.st->t_neuron = t_end;

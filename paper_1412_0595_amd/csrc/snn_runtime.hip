@@ -618,8 +618,6 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     while (n > 0) {
         a.t0 = net->t;
         a.n = std::min(n, draw ? net->res.drawn_steps : kResidentLaunch);
-        // (clusters: two steps as one and one, see k_resident's sources)
-        if (a.n == 2 && net->res.together) a.n = 1;
         a.tag0 = net->res.tag;
         a.skip_first = net->pend_delivered ? 1 : 0;
         a.drawn = draw ? net->res.d_drawn : nullptr;
