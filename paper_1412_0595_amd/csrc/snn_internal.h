@@ -275,6 +275,7 @@ struct NeuronArgs {
 constexpr int kFeatIzh = 1;       // Izhikevich populations
 constexpr int kFeatPlastic = 2;   // STDP traces and potentiation work
 constexpr int kFeatRec = 4;       // voltage sums recorded for the adjoint's loss
+constexpr int kFeatRelay = 8;     // no update: the work of S(t-1) laid out again from its spike words
 
 struct PropArgs {
     int32_t mode;
@@ -509,6 +510,10 @@ hipError_t launch_spike_totals(const Seg *segs, int32_t n_segs, const int32_t *c
                                hipStream_t s);
 // na + nb words of a and b into host memory `out` (its device address).
 hipError_t launch_read_words(const uint32_t *a, int64_t na, const uint32_t *b, int64_t nb, uint32_t *out, hipStream_t s);
+// Empty queues, and (relay) the pending work of S(t-1) laid out from its spike
+// words as the update of step t-1 in a.mode would have left it; without plastic
+// projections.
+hipError_t launch_relay(const NeuronArgs &a, int block, bool relay, hipStream_t s);
 // Zero `bytes` (a multiple of 4) at p with a kernel.
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 hipError_t launch_check_weights(const float *w, const Proj *projs, int32_t n_projs, int64_t max_nnz, uint32_t *flag,

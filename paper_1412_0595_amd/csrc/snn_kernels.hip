@@ -152,6 +152,13 @@ __device__ __forceinline__ void split_at(double x, float *hi, float *lo, uint32_
 // instantiations are held to 96 VGPRs, five wavefronts per SIMD: their state
 // is addressed as one 32-bit offset from uniform bases (ld_at/st_at), and the
 // two 8-byte spills this leaves sit outside the substep loop.
+//
+// kFeatRelay: no update; the spikes are those of the last step's words, so the
+// work items (fused: deliveries) of a step whose words alone are left come out
+// as its own update would have left them.  Launched when the step kernels take
+// over from resident steps or after spikes were set; on the device, since
+// reading the words back and building the items on the host cost more than
+// many steps and a wait for the stream.
 template <int MODE, int FEAT>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(FEAT == 0 ? 5 : 4, 8)))
 void k_neuron(NeuronArgs a)
@@ -165,7 +172,8 @@ void k_neuron(NeuronArgs a)
     const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // uniform: scalar loads below
     const int nwb = blockDim.x >> 6;
     const int64_t gw = (int64_t)blockIdx.x * nwb + wid;
-    const int64_t t = a.st->t_neuron;
+    constexpr bool kRelay = (FEAT & kFeatRelay) != 0;
+    const int64_t t = kRelay ? a.st->t_prop - 1 : a.st->t_neuron;
     const int cur = (int)(t & 1);
 
     bool spike = false;
@@ -218,7 +226,9 @@ void k_neuron(NeuronArgs a)
         // library keeps the padded neuron count below 2^29)
         const uint32_t o4 = (uint32_t)gid * 4u, o8 = (uint32_t)gid * 8u;
         const uint32_t g8 = (uint32_t)jj * 8u, s8 = (uint32_t)j * 8u;
-        if (s_kind == kHH) {
+        if constexpr (kRelay) {
+            spike = active && ((a.bits[(int64_t)cur * a.n_waves + gw] >> lane) & 1ull);
+        } else if (s_kind == kHH) {
             const double vs = s_rec ? ld_at(a.vsum, o8) : 0.0;
             double v = pair_at(a.vh, a.vl, o4);
             double m = pair_at(a.mh, a.ml, o4);
@@ -311,7 +321,7 @@ void k_neuron(NeuronArgs a)
 
         const uint64_t ball = __ballot(spike);
         wball = ball;
-        if (lane == 0) {
+        if (!kRelay && lane == 0) {
             a.bits[(int64_t)cur * a.n_waves + gw] = ball;
             if (a.raster) a.raster[(t % a.raster_steps) * a.n_waves + gw] = ball;
         }
@@ -352,7 +362,7 @@ void k_neuron(NeuronArgs a)
             }
         }
         if (ball != 0 && spike) {
-            a.counts[gid] += 1;
+            if constexpr (!kRelay) a.counts[gid] += 1;
             const uint32_t ch = (uint32_t)a.chunk;
             if constexpr (MODE != kModeTiles) {
                 // (a missing projection reads rp_pool[0..1])
@@ -1567,6 +1577,34 @@ hipError_t launch_neuron(const NeuronArgs &a, int block, hipStream_t s, hipEvent
         SNN_NEURON_FEATS(kModeFused)
 #undef SNN_NEURON_FEATS
 #undef SNN_NEURON_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// Empty queues in both slots, no population marked for pulling, and the row
+// groups of grouped mode told that both slots are done.
+__global__ __launch_bounds__(256) void k_clear_work(NeuronArgs a)
+{
+    for (int i = threadIdx.x; i < 3 * kQBuckets; i += blockDim.x) a.qb_cnt[(int64_t)i * kQBucketStride] = 0u;
+    for (int i = threadIdx.x; i < 2 * a.n_segs; i += blockDim.x) a.awcnt[i] = a.scnt[i] = a.pullf[i] = 0u;
+    if (threadIdx.x < 2) {
+        a.st->qcnt[threadIdx.x] = a.st->lcnt[threadIdx.x] = a.st->npull[threadIdx.x] = 0u;
+        a.st->grp_off[threadIdx.x] = 1u;
+    }
+}
+
+hipError_t launch_relay(const NeuronArgs &a, int block, bool relay, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_clear_work, dim3(1), dim3(256), 0, s, a);
+    const int64_t wpb = block / kWave;
+    const int64_t blocks = (a.n_waves + wpb - 1) / wpb;
+    if (!relay || blocks == 0) return hipGetLastError();
+    const dim3 g((unsigned)blocks), b(block);
+    switch (a.mode) {
+    case kModeRows: hipLaunchKernelGGL((k_neuron<kModeRows, kFeatRelay>), g, b, 0, s, a); break;
+    case kModeTiles: hipLaunchKernelGGL((k_neuron<kModeTiles, kFeatRelay>), g, b, 0, s, a); break;
+    case kModeFused: hipLaunchKernelGGL((k_neuron<kModeFused, kFeatRelay>), g, b, 0, s, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -273,6 +273,7 @@ struct snn_net {
     // the resident steps leave them), not by the queues or the fused buffer.
     bool pend_bits;
     bool pend_delivered;     // they are already in G (a switch out of fused mode)
+    bool pend_given;         // some of them were set from outside
 
     // launch shape and captured step sequences: graphs[k] replays
     // graph_len[k] whole steps (kGraphSteps, and the remainders asked for)
@@ -539,7 +540,18 @@ int materialize(snn_net *net);
 // steps in a group (a block per step and instance).
 constexpr int64_t kTapeBytes = (int64_t)512 << 20, kTapeSteps = 32768;
 
-constexpr int64_t kResidentMin = 8;        // steps in a call that are worth a cooperative launch
+// Steps in a call that are worth a resident launch.  A call and a wait,
+// resident and through the step kernels, of 1, 3 and 4 steps: 1 100 neurons 32
+// and 21 us, 38.6 and 39.2, 42 and 52; 21 000 neurons 34 and 23, 45 and 42, 48
+// and 58; 48 networks of 5 700 neurons 39 and 28, 56 and 60, 65 and 82; 300 of
+// 700 in a block each 32 and 25, 50 and 52, 59 and 70.  Calls in a row without
+// waits: 30 and 8, 36 and 25, 40 and 38; 32 and 11, 42 and 31, 47 and 44; 37
+// and 16, 54 and 48, 62 and 66; 20 and 14, 37 and 40, 46 and 56.
+constexpr int64_t kResidentMin = 4;
+// Steps in a call that are launched kernel by kernel: a graph's replay costs
+// 10 to 15 us more than its kernels where the call is waited for (1 100
+// neurons, one step 32 and 20 us, three 40.6 and 35.9, four 49 and 49.5).
+constexpr int64_t kDirectSteps = 3;
 constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
 constexpr int64_t kResidentDraw = 32;      // steps in a call whose sources are drawn ahead
 constexpr int64_t kDrawnBytes = (int64_t)64 << 20, kDrawnSteps = 2048;   // of them in a launch, at most
@@ -554,14 +566,14 @@ bool capturing(const snn_net *net)
     return c != hipStreamCaptureStatusNone;
 }
 
-// Whether a call of n steps runs resident.  A cooperative launch costs more
-// than the graph replay of a few steps, but less than laying out the pending
-// work again.
+// Whether a call of n steps runs resident: by its length, whatever ran before
+// (laying the pending work out costs the step kernels two small launches), or
+// at once where spikes were set from outside: with a tenth of 21 000 neurons
+// spiking, setting them and one step take 79 us resident and 95 through the
+// step kernels (of 1 100 neurons 48 and 45, of 85 47 and 40).
 bool use_resident(snn_net *net, int64_t n)
 {
-    if (!net->res.on || n < 1) return false;
-    if (net->res.together && n < kResidentMin && !net->pend_bits) return false;
-    return !capturing(net);
+    return net->res.on && n >= (net->pend_given ? 1 : kResidentMin) && !capturing(net);
 }
 
 // The pending deliveries are from here on those of the spike words of
@@ -626,28 +638,35 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
                                net->stream));
         if (draw) HIP_OK(launch_resident_last(a, net->res.d_draws, net->res.d_alias, net->stream));
         net->res.tag += (uint32_t)a.n;
-        net->pend_delivered = false;
+        net->pend_delivered = net->pend_given = false;
         net->t += a.n;
         n -= a.n;
     }
     return SNN_OK;
 }
 
-// n steps: resident, or as replays of captured graphs (n div 64 of the
-// 64-step graph, then one graph of the remaining n mod 64 steps).
+// n steps: resident, a few kernel by kernel, or as replays of captured graphs
+// (n div 64 of the 64-step graph, then one graph of the remaining n mod 64
+// steps).
 int run_steps(snn_net *net, int64_t n)
 {
+    if (n <= 0) return SNN_OK;
     if (use_resident(net, n))
         return run_resident(net, n, net->raster_steps > 0 ? net->raster : nullptr, std::max(net->raster_steps, 1));
-    // (laying the pending work out reads the spike words back, which would
-    // break the capture and leave the net unusable; the copies that tile mode
-    // pulls from would be brought up to date at the replay only)
-    if (n > 0 && (net->pend_bits || (net->launch.mode == kModeTiles && net->pull_stale)) && capturing(net))
+    // (a capture does not take the replays in, but would take in what lays the
+    // pending work out and brings the copies that tile mode pulls from up to
+    // date, and run it at its own replays only)
+    const bool captured = capturing(net);
+    if (captured && (net->pend_bits || (net->launch.mode == kModeTiles && net->pull_stale)))
         return fail(SNN_EINVAL, "the stream is being captured while work for the next step is still to be laid out");
-    int rc = n > 0 ? materialize(net) : SNN_OK;
-    if (!rc) rc = prepare_graphs(net, n);
+    int rc = materialize(net);
     if (rc) return rc;
-    if (n > 0) net->pend_delivered = false;
+    net->pend_delivered = false;
+    if (n <= kDirectSteps && !captured) {
+        for (; n > 0; --n, ++net->t) HIP_OK(enqueue_step(net, net->stream));
+        return SNN_OK;
+    }
+    if ((rc = prepare_graphs(net, n))) return rc;
     hipGraphExec_t g = nullptr;
     if (n >= kGraphSteps) {
         if ((rc = graph_for(net, kGraphSteps, &g))) return rc;
@@ -833,7 +852,7 @@ static int timed_on_snapshot(snn_net *net, F body, double *ms_out)
         return fail(SNN_ENOMEM, "snapshot allocation failed");
     }
     const int64_t t_saved = net->t;
-    const bool bits_saved = net->pend_bits, delivered_saved = net->pend_delivered;
+    const bool bits_saved = net->pend_bits, delivered_saved = net->pend_delivered, given_saved = net->pend_given;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = SNN_OK;
     hipError_t e = hipMemcpyAsync(snap, net->d_arena, (size_t)net->arena_bytes, hipMemcpyDeviceToDevice, net->stream);
@@ -852,6 +871,7 @@ static int timed_on_snapshot(snn_net *net, F body, double *ms_out)
     net->t = t_saved;
     net->pend_bits = bits_saved;
     net->pend_delivered = delivered_saved;
+    net->pend_given = given_saved;
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipFree(snap);
@@ -2307,20 +2327,9 @@ int materialize(snn_net *net)
     int rc;
     if (net->launch.mode == kModeTiles && (rc = refresh_pull(net))) return rc;
     if (!net->pend_bits) return SNN_OK;
-    if (net->pend_delivered) {
-        // nothing is pending: empty queues, as the switch out of fused mode left them
-        rc = clear_queues(net);
-        if (!rc) net->pend_bits = false;
-        return rc;
-    }
-    if ((rc = clear_queues(net))) return rc;
-    const int mode = net->launch.mode;
-    if (mode == kModeFused) net->launch.mode = kModeRows;
-    rc = rebuild_pending(net, -1, nullptr);
-    net->launch.mode = mode;
-    if (!rc && mode == kModeFused) rc = deliver_queued_to_fused(net, kModeRows);
-    if (!rc) net->pend_bits = false;
-    return rc;
+    HIP_OK(launch_relay(neuron_args(net), net->launch.neuron_block, !net->pend_delivered, net->stream));
+    net->pend_bits = net->pend_given = false;
+    return SNN_OK;
 }
 
 }  // namespace
@@ -2348,6 +2357,7 @@ int snn_set_last_spikes(snn_net *net, int32_t inst, int32_t pop, const uint8_t *
         // the resident steps deliver from the words themselves
         if ((rc = pending_to_bits(net))) return rc;
         net->pend_delivered = false;
+        net->pend_given = true;
         return SNN_OK;
     }
     if ((rc = materialize(net))) return rc;
@@ -2529,7 +2539,9 @@ int snn_time_steps(snn_net *net, int64_t n_steps, double *out_ms)
     if (rc) return rc;
     if (n_steps < 1 || !out_ms) return fail(SNN_EINVAL, "need n_steps >= 1 and an output");
     // capture the graph before the clock starts: host capture time is not step time
-    if (!use_resident(net, n_steps) && ((rc = materialize(net)) || (rc = prepare_graphs(net, n_steps)))) return rc;
+    if (!use_resident(net, n_steps) &&
+        ((rc = materialize(net)) || (n_steps > kDirectSteps && (rc = prepare_graphs(net, n_steps)))))
+        return rc;
     double ms = 0.0;
     rc = timed_on_snapshot(net, [&]() { return run_steps(net, n_steps); }, &ms);
     if (rc) return rc;
@@ -2628,7 +2640,7 @@ int snn_reset(snn_net *net)
     HIP_OK(hipMemcpyAsync(net->vh, net->d_init_state, 4 * 8 * (size_t)net->n_neurons_padded, hipMemcpyDeviceToDevice,
                           net->stream));
     net->t = 0;
-    net->pend_bits = net->pend_delivered = false;
+    net->pend_bits = net->pend_delivered = net->pend_given = false;
     return SNN_OK;
 }
 

@@ -302,3 +302,28 @@ def test_even_calls_keep_the_words_they_begin_with(snn, name):
         got.append(out)
         net.close()
     assert not differing(*got)
+
+
+@pytest.mark.parametrize("name", ["word_edges", "split", "many", "izh"])
+def test_short_calls_between_long_ones(snn, name):
+    """Calls of a few steps go through the step kernels, which take the
+    pending work over from resident steps and from spikes set from outside,
+    and hand it back."""
+    print(f"case: resident short calls {name}", flush=True)
+    spec = NETS[name]()
+    rng = np.random.default_rng(6)
+    flags = [(rng.random(p["n"]) < 0.3).astype(np.uint8) for p in spec["instances"][0]["pops"]]
+
+    def run(net):
+        for n in (3, 64, 1, 1, 2, 4, 3, 5, 1):
+            net.step(n)
+        for n in (1, 2, 64):
+            for p, f in enumerate(flags):
+                net.set_last_spikes(0, p, f)
+            net.step(n)
+            net.step(3)
+    net = snn.Network(spec)
+    run(net)
+    got = everything(net, spec)
+    net.close()
+    assert not differing(got, by_modes(snn, spec, dict(mode=0), run))
