@@ -166,6 +166,7 @@ struct snn_net {
     hipStream_t stream;
     hipStream_t cap_stream;
     void *h_stage, *d_stage;         // pinned host memory for small reads, and its device address
+    std::recursive_mutex read_lock;  // holds h_stage and d_totals for one read: threads may read at once
     snn_alloc_fn alloc_fn;
     snn_free_fn free_fn;
     void *alloc_ctx;
@@ -711,6 +712,7 @@ int d2h(snn_net *net, void *dst, const void *src, size_t bytes, void *dst2 = nul
 {
     if (bytes + bytes2 == 0) return SNN_OK;
     if (net->h_stage && bytes + bytes2 <= kStageBytes && (bytes | bytes2) % 4 == 0) {
+        std::lock_guard<std::recursive_mutex> hold(net->read_lock);
         HIP_OK(launch_read_words((const uint32_t *)src, (int64_t)(bytes / 4), (const uint32_t *)src2, (int64_t)(bytes2 / 4),
                                  (uint32_t *)net->d_stage, net->stream));
         HIP_OK(hipStreamSynchronize(net->stream));
@@ -1595,6 +1597,7 @@ int snn_get_spike_totals(snn_net *net, int32_t pop, int64_t *totals)
         const int s = seg_index(net, b, pop, false);
         if (s < 0) return s;
     }
+    std::lock_guard<std::recursive_mutex> hold(net->read_lock);
     HIP_OK(launch_spike_totals(net->d_segs, (int32_t)net->segs.size(), net->counts, pop, net->d_totals, net->stream));
     return d2h(net, totals, net->d_totals, 8 * (size_t)net->n_inst);
 }

@@ -327,3 +327,31 @@ def test_short_calls_between_long_ones(snn, name):
     got = everything(net, spec)
     net.close()
     assert not differing(got, by_modes(snn, spec, dict(mode=0), run))
+
+
+def test_several_threads_read_one_network(snn):
+    """Readers of one network on threads of their own each get their own
+    array (small reads share the network's staging memory)."""
+    import threading
+    print("case: resident readers", flush=True)
+    spec = layered(3, 100, 1000, 70)
+    net = snn.Network(spec)
+    net.step(200)
+    reads = [lambda b=b, p=p, v=v: net.state(b, p, v) for b in range(3) for p in (1, 2) for v in range(4)]
+    reads += [lambda b=b, p=p: net.spikes(b, p) for b in range(3) for p in range(3)]
+    reads += [lambda p=p: net.spike_totals(p) for p in range(3)]
+    want = [r() for r in reads]
+    wrong = []
+
+    def run(k):
+        for i in range(300):
+            at = (7 * k + i) % len(reads)
+            if not np.array_equal(reads[at](), want[at]):
+                wrong.append(at)
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    net.close()
