@@ -146,7 +146,8 @@ typedef void (*snn_free_fn)(void *ptr, void *ctx);
  *  autotune      1: time candidate launch shapes on this network at create
  *                and keep the fastest (results do not depend on it)
  *  tune_cache    path of a JSON file that stores tuned shapes per network
- *                signature, or NULL */
+ *                signature, and whether resident steps were faster than the
+ *                step kernels, or NULL */
 typedef struct {
     double dt_ms;
     int32_t substeps;

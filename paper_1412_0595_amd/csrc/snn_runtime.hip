@@ -2982,7 +2982,10 @@ static std::string signature(const snn_net *net)
     return buf;
 }
 
-static bool cache_lookup(const char *path, const std::string &sig, snn_launch *out)
+// A line of the cache: the launch shape and, where both were measured, whether
+// resident stepping was faster (*resident: 1 or 0, -1 if the line has no such
+// number).
+static bool cache_lookup(const char *path, const std::string &sig, snn_launch *out, int *resident)
 {
     if (!path) return false;
     FILE *f = fopen(path, "r");
@@ -2992,9 +2995,11 @@ static bool cache_lookup(const char *path, const std::string &sig, snn_launch *o
     while (fgets(line, sizeof line, f)) {
         char key[300];
         snn_launch L{};
-        if (sscanf(line, " \"%299[^\"]\" : [ %d , %d , %d , %d , %d ]", key, &L.neuron_block, &L.prop_blocks,
-                   &L.prop_block, &L.chunk, &L.mode) == 6 && sig == key) {
+        int r = -1;
+        if (sscanf(line, " \"%299[^\"]\" : [ %d , %d , %d , %d , %d , %d ]", key, &L.neuron_block, &L.prop_blocks,
+                   &L.prop_block, &L.chunk, &L.mode, &r) >= 6 && sig == key) {
             *out = L;
+            *resident = r;
             found = true;
         }
     }
@@ -3002,7 +3007,7 @@ static bool cache_lookup(const char *path, const std::string &sig, snn_launch *o
     return found;
 }
 
-static void cache_store(const char *path, const std::string &sig, const snn_launch &L)
+static void cache_store(const char *path, const std::string &sig, const snn_launch &L, int resident)
 {
     if (!path) return;
     std::vector<std::string> keep;
@@ -3018,8 +3023,8 @@ static void cache_store(const char *path, const std::string &sig, const snn_laun
         fclose(f);
     }
     char buf[512];
-    snprintf(buf, sizeof buf, "  \"%s\": [%d, %d, %d, %d, %d]", sig.c_str(), L.neuron_block, L.prop_blocks, L.prop_block,
-             L.chunk, L.mode);
+    snprintf(buf, sizeof buf, "  \"%s\": [%d, %d, %d, %d, %d%s]", sig.c_str(), L.neuron_block, L.prop_blocks, L.prop_block,
+             L.chunk, L.mode, resident < 0 ? "" : resident ? ", 1" : ", 0");
     keep.push_back(buf);
     if (FILE *f = fopen(path, "w")) {
         fprintf(f, "{\n");
@@ -3032,21 +3037,28 @@ static void cache_store(const char *path, const std::string &sig, const snn_laun
 int snn_autotune_internal(snn_net *net, const char *cache)
 {
     const std::string sig = signature(net);
+    const int64_t steps = 3 * kGraphSteps;
     snn_launch best = net->launch;
-    int rc;
-    if (cache_lookup(cache, sig, &best)) {
+    int rc, resident = -1;
+    double best_ms = 0.0, resident_ms = 0.0;
+    const bool hit = cache_lookup(cache, sig, &best, &resident);
+    if (hit && (!net->res.ok || resident >= 0)) {
         if ((rc = snn_set_launch(net, &best))) return rc;
-        net->res.on = net->res.ok;
+        net->res.on = net->res.ok && resident != 0;
         return SNN_OK;
     }
-    const int64_t steps = 3 * kGraphSteps;
-    double best_ms = 0.0, resident_ms = 0.0;
-    if (net->res.on && (rc = snn_time_steps(net, steps, &resident_ms))) return rc;   // (warm-up)
-    if (net->res.on && (rc = snn_time_steps(net, steps, &resident_ms))) return rc;
+    for (int k = 0; k < 2 && net->res.on; ++k)   // (the first is a warm-up)
+        if ((rc = snn_time_steps(net, steps, &resident_ms))) return rc;
     net->res.on = false;
-    rc = snn_time_steps(net, steps, &best_ms);   // also warms up
-    if (rc) return rc;
-    if ((rc = snn_time_steps(net, steps, &best_ms))) return rc;
+    if (hit && (rc = snn_set_launch(net, &best))) return rc;
+    for (int k = 0; k < 2; ++k)
+        if ((rc = snn_time_steps(net, steps, &best_ms))) return rc;
+    if (hit) {
+        // a line without the comparison, which is added to it
+        net->res.on = resident_ms < best_ms;
+        cache_store(cache, sig, best, net->res.on);
+        return SNN_OK;
+    }
     // modes: rows, tiles, fused (no plastic projections), grouped (some projection to group)
     int md[4] = {kModeRows, kModeTiles, 0, 0}, n_md = 2;
     if (!net->plastic) md[n_md++] = kModeFused;
@@ -3076,6 +3088,6 @@ int snn_autotune_internal(snn_net *net, const char *cache)
     }
     if ((rc = snn_set_launch(net, &best))) return rc;
     net->res.on = net->res.ok && resident_ms < best_ms;
-    cache_store(cache, sig, best);
+    cache_store(cache, sig, best, net->res.ok ? (int)net->res.on : -1);
     return SNN_OK;
 }

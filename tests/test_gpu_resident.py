@@ -355,3 +355,56 @@ def test_several_threads_read_one_network(snn):
         t.join()
     assert not wrong
     net.close()
+
+
+def steps_resident(snn, net, stream):
+    """Whether the network's long calls run resident: stepping while the
+    stream is captured is refused after such a call alone."""
+    import torch
+    net.step(64)
+    net.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="thread_local"):
+        try:
+            net.step(1)
+        except snn.SNNError:
+            return True
+    return False
+
+
+@pytest.mark.parametrize("mode", range(4))
+def test_tune_cache_keeps_the_choice(snn, tmp_path, mode):
+    """A cached network takes the path that the line names, in every mode of
+    its step kernels; a line without that number keeps its shape and gets it."""
+    import torch
+    print(f"case: resident tune cache {mode}", flush=True)
+    spec = layered(1, 100, 500, 50)
+    path = tmp_path / "tune.json"
+    snn.Network(spec, autotune=True, tune_cache=path).close()
+    line = next(x for x in path.read_text().splitlines() if "[" in x)
+    key, tuned = line[:line.index("[")], [int(x) for x in line[line.index("[") + 1:line.index("]")].split(",")]
+    assert len(tuned) == 6 and tuned[5] in (0, 1)
+    shape = [256, 1024, 256, 256, mode]
+
+    def run(net):
+        for n in (64, 1, 3, 40, 2):
+            net.step(n)
+        net.set_last_spikes(0, 1, np.ones(500, np.uint8))
+        net.step(1)
+        net.step(2)
+    ref = by_modes(snn, spec, dict(mode=0), run)
+    for numbers, want in ((shape + [0], False), (shape + [1], True), (shape, None)):
+        path.write_text("{\n%s%s\n}\n" % (key, numbers))
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            net = snn.Network(spec, autotune=True, tune_cache=path, stream=stream)
+            assert list(net.launch.values()) == shape
+            run(net)
+            assert not differing(ref, everything(net, spec)), numbers
+            got = steps_resident(snn, net, stream)
+            net.close()
+        if want is None:
+            now = [int(x) for x in path.read_text().split("[")[1].split("]")[0].split(",")]
+            assert now == shape + [int(got)]
+        else:
+            assert got == want, numbers
