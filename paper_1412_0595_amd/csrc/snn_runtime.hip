@@ -137,8 +137,8 @@ struct HostProj {            // host copy of what state access needs
 
 // Resident stepping: the words of every instance dealt out over blocks.
 struct ResidentPlan {
-    bool ok;                 // the network fits and is expected to step faster this way
-    bool on;                 // used by the steps (off: the launch shape was set by the caller, or measured faster)
+    bool ok;                 // the tables are there: the network fits and is expected to step faster this way
+    bool on;                 // used by the steps (off while the tuner measures the step kernels)
     int blocks, block;
     size_t lds;
     bool together;           // some cluster has several blocks: all must be resident (cooperative launch)
@@ -1744,6 +1744,19 @@ int snn_get_last_spikes(snn_net *net, int32_t inst, int32_t pop, uint8_t *out)
     return SNN_OK;
 }
 
+// Gives the resident tables back (a second copy of the connectivity): they are
+// of no more use once the step kernels are chosen.  Nothing may be running that
+// reads them.
+static void drop_resident(snn_net *net)
+{
+    ResidentPlan &R = net->res;
+    for (void *p : {(void *)R.d_blocks, (void *)R.d_words, (void *)R.d_feeds, (void *)R.d_sources, (void *)R.d_draws,
+                    (void *)R.d_alias, (void *)R.d_drawn_at, (void *)R.d_drawn, (void *)R.d_wfeeds, (void *)R.d_reads,
+                    (void *)R.d_bounds, (void *)R.d_from, (void *)R.d_syn, (void *)R.d_xbuf})
+        dev_free(net, p);
+    R = ResidentPlan{};
+}
+
 // ------------------------------ resident plan --------------------------------
 // Deals the words of every instance out over the blocks of its cluster and
 // builds the blocks' tables.  A step takes a block about as long for one word
@@ -2069,10 +2082,8 @@ static int plan_resident(snn_net *net)
     if (!R.d_blocks || !R.d_words || !R.d_feeds || !R.d_wfeeds || !R.d_sources || !R.d_reads || !R.d_bounds || !R.d_from ||
         !R.d_syn || !R.d_xbuf || !d_totals || !R.d_draws || !R.d_alias || !R.d_drawn_at) {
         // no room for the tables: the step kernels do without them
-        for (void *p : {(void *)R.d_blocks, (void *)R.d_words, (void *)R.d_feeds, (void *)R.d_wfeeds, (void *)R.d_sources,
-                        (void *)R.d_reads, (void *)R.d_bounds, (void *)R.d_from, (void *)R.d_syn, (void *)R.d_xbuf,
-                        (void *)d_totals, (void *)R.d_draws, (void *)R.d_alias, (void *)R.d_drawn_at, (void *)R.d_drawn})
-            dev_free(net, p);
+        dev_free(net, d_totals);
+        drop_resident(net);
         return SNN_OK;
     }
     for (size_t k = 0; k < feeds.size(); ++k) feeds[k].bounds = R.d_bounds + sources[k].bounds0;
@@ -2093,7 +2104,10 @@ static int plan_resident(snn_net *net)
     if ((rc = d2h(net, totals.data(), d_totals, 8 * totals.size()))) return rc;
     dev_free(net, d_totals);
     for (size_t k = 0; k < blocks.size(); ++k) {
-        if (totals[k] >= ((int64_t)1 << 31)) return SNN_OK;
+        if (totals[k] >= ((int64_t)1 << 31)) {
+            drop_resident(net);
+            return SNN_OK;
+        }
         blocks[k].syn0 = syn_total;
         syn_total += totals[k];
     }
@@ -2487,10 +2501,10 @@ int snn_get_launch(const snn_net *net, snn_launch *out)
     return SNN_OK;
 }
 
-int snn_set_launch(snn_net *net, const snn_launch *in)
+// snn_set_launch, but for the resident tables.
+static int set_launch(snn_net *net, const snn_launch *in)
 {
-    int rc = check_net(net);
-    if (rc) return rc;
+    int rc;
     if (!in) return fail(SNN_EINVAL, "in is NULL");
     if (in->neuron_block < 64 || in->neuron_block > 1024 || in->neuron_block % 64)
         return fail(SNN_EINVAL, "neuron_block must be a multiple of 64 in [64, 1024]");
@@ -2507,7 +2521,7 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
         return fail(SNN_EINVAL, "mode 2 (fused) needs a network without plastic projections");
     const snn_launch prev = net->launch;
     net->launch = *in;
-    net->res.on = false;      // a shape given by the caller is the one that runs
+    net->res.on = false;
     if ((rc = update_qbuckets(net))) return rc;
     if (net->pend_bits) {
         if ((rc = materialize(net))) return rc;
@@ -2533,6 +2547,18 @@ int snn_set_launch(snn_net *net, const snn_launch *in)
     if (rc) return rc;
     if ((rc = materialize(net))) return rc;
     drop_graphs(net);
+    return SNN_OK;
+}
+
+int snn_set_launch(snn_net *net, const snn_launch *in)
+{
+    int rc = check_net(net);
+    if (rc) return rc;
+    if ((rc = set_launch(net, in))) return rc;
+    if (!net->res.ok) return SNN_OK;
+    // a shape given by the caller is the one that runs from here on
+    HIP_OK(hipStreamSynchronize(net->stream));
+    drop_resident(net);
     return SNN_OK;
 }
 
@@ -3034,7 +3060,7 @@ static void cache_store(const char *path, const std::string &sig, const snn_laun
     }
 }
 
-int snn_autotune_internal(snn_net *net, const char *cache)
+static int autotune(snn_net *net, const char *cache)
 {
     const std::string sig = signature(net);
     const int64_t steps = 3 * kGraphSteps;
@@ -3043,14 +3069,14 @@ int snn_autotune_internal(snn_net *net, const char *cache)
     double best_ms = 0.0, resident_ms = 0.0;
     const bool hit = cache_lookup(cache, sig, &best, &resident);
     if (hit && (!net->res.ok || resident >= 0)) {
-        if ((rc = snn_set_launch(net, &best))) return rc;
+        if ((rc = set_launch(net, &best))) return rc;
         net->res.on = net->res.ok && resident != 0;
         return SNN_OK;
     }
     for (int k = 0; k < 2 && net->res.on; ++k)   // (the first is a warm-up)
         if ((rc = snn_time_steps(net, steps, &resident_ms))) return rc;
     net->res.on = false;
-    if (hit && (rc = snn_set_launch(net, &best))) return rc;
+    if (hit && (rc = set_launch(net, &best))) return rc;
     for (int k = 0; k < 2; ++k)
         if ((rc = snn_time_steps(net, steps, &best_ms))) return rc;
     if (hit) {
@@ -3076,7 +3102,7 @@ int snn_autotune_internal(snn_net *net, const char *cache)
             if (dim == 1) L.neuron_block = vals[k];
             if (dim == 2) L.prop_blocks = vals[k];
             if (dim == 3) L.chunk = vals[k];
-            if ((rc = snn_set_launch(net, &L))) return rc;
+            if ((rc = set_launch(net, &L))) return rc;
             double ms = 0.0;
             if ((rc = snn_time_steps(net, steps, &ms))) return rc;
             if (ms < best_ms) {
@@ -3086,8 +3112,17 @@ int snn_autotune_internal(snn_net *net, const char *cache)
         }
         best = cur_best;
     }
-    if ((rc = snn_set_launch(net, &best))) return rc;
+    if ((rc = set_launch(net, &best))) return rc;
     net->res.on = net->res.ok && resident_ms < best_ms;
     cache_store(cache, sig, best, net->res.ok ? (int)net->res.on : -1);
+    return SNN_OK;
+}
+
+int snn_autotune_internal(snn_net *net, const char *cache)
+{
+    int rc = autotune(net, cache);
+    if (rc || !net->res.ok || net->res.on) return rc;
+    HIP_OK(hipStreamSynchronize(net->stream));
+    drop_resident(net);
     return SNN_OK;
 }

@@ -408,3 +408,31 @@ def test_tune_cache_keeps_the_choice(snn, tmp_path, mode):
             assert now == shape + [int(got)]
         else:
             assert got == want, numbers
+
+
+def test_tables_given_back(snn, tmp_path):
+    """The resident tables (8 bytes per synapse and more) go when the step
+    kernels are chosen: by the caller, or by the line of a tune cache."""
+    import torch
+    print("case: resident tables given back", flush=True)
+    spec = layered(1, 300, 3000, 257)
+    path = tmp_path / "tune.json"
+    used = torch.cuda.memory_allocated
+    base = used()
+    net = snn.Network(spec, autotune=True, tune_cache=path)
+    net.step(40)
+    full = used()
+    net.set_launch(mode=0)
+    assert used() <= full - 8 * net.weight_count
+    net.step(40)
+    net.set_launch(mode=2)
+    net.step(40)
+    got = everything(net, spec)
+    net.close()
+    assert used() == base
+    path.write_text(path.read_text().replace(", 1]", ", 0]"))
+    net = snn.Network(spec, autotune=True, tune_cache=path)
+    assert used() <= base + (full - base) - 8 * net.weight_count
+    net.step(120)
+    assert not differing(got, everything(net, spec))
+    net.close()
