@@ -32,8 +32,11 @@ def sweep_table(net, spec, pop=None):
     pop = spec.get("pop", 1) if pop is None else pop
     n_conn = np.asarray(spec["n_conn"], np.float64)
     g_scale = np.array([swept_scale(inst) for inst in spec["instances"]], np.float64)
-    size = np.array([inst["pops"][pop]["n"] for inst in spec["instances"]], np.float64)
-    avg = net.spike_totals(pop) / size
+    if len(spec["instances"]) == net.n_instances:
+        size = np.array([inst["pops"][pop]["n"] for inst in spec["instances"]], np.float64)
+        avg = net.spike_totals(pop) / size
+    else:                                       # the table of the network's first runs
+        avg = np.array([net.spikes(k, pop).mean() for k in range(len(spec["instances"]))], np.float64)
     return n_conn, g_scale, avg, net.nan_counts()
 
 

@@ -153,3 +153,25 @@ def test_fit_never_worse_than_oracle_on_random_laws():
         assert f_got <= f_want * (1 + 1e-9) + 1e-24 * float(np.dot(y, y)), (k, got, want)
         fitted += 1
     assert fitted >= 20 and ranged <= fitted // 5, (fitted, ranged)
+
+
+@pytest.mark.parametrize("runs", [1, 2, 3])
+def test_sweep_table_of_the_first_runs(runs):
+    """A spec of a network's first runs gives one average per run of the spec."""
+    from paper_1412_0595_amd import calibrate
+    counts = [np.array([3, 0, 6], np.int32), np.array([1, 1], np.int32), np.array([5, 2, 2, 3], np.int32)]
+
+    class Net:
+        n_instances = 3
+
+        def spikes(self, inst, pop):
+            return counts[inst]
+
+        def spike_totals(self, pop):
+            return np.array([c.sum() for c in counts], np.int64)
+
+        def nan_counts(self):
+            return np.zeros(3, np.int32)
+    spec = dict(n_conn=[100.0] * runs, instances=[
+        dict(g_scale=1.0, pops=[dict(n=c.size)], projs=[]) for c in counts[:runs]])
+    assert calibrate.sweep_table(Net(), spec, pop=0)[2].tolist() == [3.0, 1.0, 3.0][:runs]

@@ -304,13 +304,19 @@ def test_even_calls_keep_the_words_they_begin_with(snn, name):
     assert not differing(*got)
 
 
-@pytest.mark.parametrize("name", ["word_edges", "split", "many", "izh"])
+def singles():
+    """More networks than compute units, each in a block of its own."""
+    base = layered(1, 70, 200, 20)["instances"][0]
+    return dict(dt=0.1, substeps=3, instances=[dict(base, seed=netgen.instance_seed(11, i)) for i in range(300)])
+
+
+@pytest.mark.parametrize("name", ["word_edges", "split", "singles", "izh"])
 def test_short_calls_between_long_ones(snn, name):
     """Calls of a few steps go through the step kernels, which take the
     pending work over from resident steps and from spikes set from outside,
     and hand it back."""
     print(f"case: resident short calls {name}", flush=True)
-    spec = NETS[name]()
+    spec = singles() if name == "singles" else NETS[name]()
     rng = np.random.default_rng(6)
     flags = [(rng.random(p["n"]) < 0.3).astype(np.uint8) for p in spec["instances"][0]["pops"]]
 
