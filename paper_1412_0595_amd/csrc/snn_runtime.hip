@@ -156,6 +156,7 @@ struct ResidentPlan {
     int32_t *d_bounds, *d_from;
     int2 *d_syn;
     uint64_t *d_xbuf;
+    int64_t x_total;         // its words
 };
 
 struct snn_net {
@@ -555,6 +556,10 @@ constexpr int64_t kResidentMin = 4;
 constexpr int64_t kDirectSteps = 3;
 constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
 constexpr int64_t kResidentDraw = 32;      // steps in a call whose sources are drawn ahead
+// Exchange tags compare as signed differences, and a slot of the ring may keep
+// its value for long (calls with sources drawn ahead leave the sources' slots
+// alone), so after this many steps the ring is cleared and the tags begin anew.
+constexpr uint32_t kResidentTags = 1u << 20;
 constexpr int64_t kDrawnBytes = (int64_t)64 << 20, kDrawnSteps = 2048;   // of them in a launch, at most
 
 bool capturing(const snn_net *net)
@@ -629,6 +634,10 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     a.n_drawn = net->res.n_drawn;
     a.drawn_at = net->res.d_drawn_at;
     while (n > 0) {
+        if (net->res.tag > kResidentTags) {
+            HIP_OK(launch_fill_zero(net->res.d_xbuf, 8 * (size_t)net->res.x_total, net->stream));
+            net->res.tag = 1;
+        }
         a.t0 = net->t;
         a.n = std::min(n, draw ? net->res.drawn_steps : kResidentLaunch);
         a.tag0 = net->res.tag;
@@ -2034,6 +2043,7 @@ static int plan_resident(snn_net *net)
         if (M > 1) x_total += (int64_t)kResRing * 2 * I.n_words;
         R.together |= M > 1;
     }
+    R.x_total = x_total;
     R.blocks = (int)best.blocks;
     // slice bounds in LDS as far as they fit, neurons' first
     const int64_t room = R.blocks > n_cu ? kResLds / 2 : kResLds;

@@ -442,3 +442,23 @@ def test_tables_given_back(snn, tmp_path):
     net.step(120)
     assert not differing(got, everything(net, spec))
     net.close()
+
+
+def test_tags_begin_anew(snn):
+    """The exchange's tags begin anew every 2^20 steps: long calls up to and
+    beyond that, short ones, whose sources go through the exchange again, and
+    long ones."""
+    print("case: resident tags", flush=True)
+    spec = layered(1, 70, 130, 20)
+    got = []
+    for mode in (None, dict(mode=2)):
+        net = snn.Network(spec)
+        if mode:
+            net.set_launch(**mode)
+        net.step(30)
+        net.step((1 << 20) - 100)
+        for n in [5] * 30 + [700, 17, 31]:
+            net.step(n)
+        got.append(everything(net, spec))
+        net.close()
+    assert not differing(*got)
