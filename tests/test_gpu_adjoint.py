@@ -223,3 +223,61 @@ def test_adjoint_full_size_sampled(snn):
             say(f"    projection {q}: |dg gpu - oracle| / |dg oracle| = {rel:.2e}")
             assert rel <= 1e-3
     net.close()
+
+
+def test_groups_of_different_sizes(snn):
+    """The backward pass in groups of two segments (what the no-allocation
+    entry point's 64 MiB hold) and of all three (the network's own tape of up
+    to 512 MiB): the adjoint carried from group to group, the checkpoints of a
+    later group, a last segment that is shorter, and segments of more steps
+    than the gather holds spike words of (2 048).  Bitwise but for dL/dg_scale,
+    whose double atomics are unordered: a few sums of some hundred terms each,
+    so within 1e-12."""
+    import torch
+    say("case: adjoint, groups of 2 and 1 segments and of 3")
+    rng = np.random.default_rng(11)
+    spec = dict(dt=0.1, substeps=3, instances=[
+        netgen.layered_instance(rng, 60 + 3 * i, 300 + 70 * i, 120 + i, rate_hz=40.0, p_ab=0.3, p_bc=0.5,
+                                seed=netgen.instance_seed(11, i)) for i in range(2)])
+    T, K, n_loss, n_in = 5200, 2100, 241, 2
+    segment = 8 * n_loss * K * (4 + 2 * n_in)
+    assert -(-T // K) == 3 and (64 << 20) // segment == 2 and (512 << 20) // segment >= 3
+    net = snn.Network(spec, record_vbar=("C",))
+    vb = net.forward_record(2, T, K)
+    dv = vb - vb.mean()
+    dg, ds, bad = net.backward(dv, check=True)
+    dg2, ds2 = torch.empty_like(dg), torch.empty_like(ds)
+    net.backward_noalloc(dv, dg2, ds2)
+    assert bad == 0 and float(dg.abs().sum()) > 0
+    assert torch.equal(dg, dg2)
+    assert torch.allclose(ds, ds2, rtol=1e-12, atol=0.0)
+    net.close()
+
+
+def test_long_segment_matches_fp64_oracle(snn):
+    """A segment of more steps than the gather holds spike words of (2 048),
+    and a short one after it, against the oracle adjoint; bounds as above."""
+    import torch
+    say("case: adjoint, 1 instance of the adjoint workload at scale 0.1, T=2600, K=2300")
+    spec = _spec(1, 0.1)
+    T, K = 2600, 2300
+    net = snn.Network(spec, record_vbar=("C",))
+    vb = net.forward_record(2, T, K).cpu().numpy()
+    L, dv = _loss_grad(vb, spec)
+    dg, ds, mism = net.backward(torch.tensor(dv, device=net.device), check=True)
+    assert mism == 0
+    inst = spec["instances"][0]
+    ro, ri = _oracle_raster(net, spec, 0, T)
+    orc = O.OracleNet(inst)
+    for p in (1, 2):
+        orc.set_replay(p, ro, ri, T)
+    vb_o, grads, ds_o = orc.adjoint(T, 2, dv)
+    assert np.max(np.abs(vb_o - vb)) < 1e-3
+    assert abs(float(ds[0]) - ds_o) <= 1e-3 * abs(ds_o)
+    for q in (1, 2):
+        o = net.weight_offset(0, q)
+        gq = dg[o:o + inst["projs"][q]["col_idx"].size].cpu().numpy().astype(np.float64)
+        rel = np.linalg.norm(gq - grads[q]) / np.linalg.norm(grads[q])
+        say(f"    projection {q}: |dg gpu - oracle| / |dg oracle| = {rel:.2e}")
+        assert rel <= 1e-3
+    net.close()
