@@ -1770,16 +1770,24 @@ static void drop_resident(snn_net *net)
 // Deals the words of every instance out over the blocks of its cluster and
 // builds the blocks' tables.  A step takes a block about as long for one word
 // as for one per SIMD, and then longer with every word, while more blocks
-// lengthen the exchange little: 1 100 neurons take 3.6 us a step in 5 blocks,
-// 4.6 in 3, 5.5 in 2, 7.4 in one; 21 000 take 5.7 in 84, 6.8 in 56, 7.7 in 42,
-// 9.2 in 24; a sweep of 100 networks 7.6 in 200, 11.5 in 100.  So the blocks
+// lengthen the exchange little: 1 100 neurons take 3.1 us a step in 7 blocks,
+// 3.4 in 5, 3.9 in 3, 4.4 in 2, 6.7 in one; 21 000 take 4.3 in 96, 4.7 in 64,
+// 4.9 in 43, 5.7 in 32, 8.2 in 20; a sweep of 100 networks 5.7 in 250, 6.5 in
+// 200, 10.2 in 100.  So the blocks
 // are as many as are resident together at one per compute unit, down to four
 // words each; where the instances alone are more, each keeps to one block.
 // Networks that do not fit (LDS: 3.2 to 5 KiB per word), with plastic
 // projections, or whose estimate (2 us, and 4 for every 16 words of a block,
 // times the blocks per compute unit) is not below the step kernels' (7 us and
 // 2.5 ns per word, measured on batches of 20 to 256 instances) keep the step
-// kernels.
+// kernels.  The estimates also hold the expected spikes (sources at their
+// rates, neurons at 20 a second): every block of a cluster reads all of its
+// words (1 ns each) and walks the slices of all spiking rows (14 ns each),
+// which the step kernels spread over the chip (0.1 ns per synapse, 40 ns for
+// every one that the same neuron gets in a step).  Without that, 300 000
+// sources of 200 Hz onto 1 000 neurons took 72 us a step here and 16 there,
+// 100 000 took 33 and 15; 20 000 take 9.2 and 12.9, and 20 000 of 1 000 Hz onto
+// 64 neurons 33 and 51.  (A microsecond of it is in the 2 us already.)
 static int plan_resident(snn_net *net)
 {
     ResidentPlan &R = net->res;
@@ -1794,7 +1802,8 @@ static int plan_resident(snn_net *net)
     }
     const int n_cu = prop.multiProcessorCount;
 
-    struct Inst { int64_t w_first, n_words, n_state, n_poi, nnz; double load, read_load; };
+    // rows: expected spikes per step with synapses to deliver
+    struct Inst { int64_t w_first, n_words, n_state, n_poi, nnz; double load, read_load, rows; };
     std::vector<Inst> in(net->n_inst);
     auto reads_neurons = [&](const Seg &S) {
         for (int q = 0; q < S.n_in; ++q) {
@@ -1811,7 +1820,10 @@ static int plan_resident(snn_net *net)
         if (S.kind == kPoisson) return 0.3;
         return (S.kind == kHH ? 1.0 : 0.3) + (reads_neurons(S) ? 3.0 : 0.0);
     };
-    double step_kernels = 7.0;
+    auto spikes_per_step = [&](const Seg &S) {
+        return (double)S.n * (S.kind == kPoisson ? std::min(1.0, std::ldexp((double)S.thresh, -32)) : 0.02 * net->dt);
+    };
+    double step_kernels = 7.0, synapses = 0.0, most = 0.0;   // delivered in a step: in all, onto one neuron
     for (int b = 0; b < net->n_inst; ++b) {
         Inst &I = in[b];
         I = Inst{};
@@ -1825,6 +1837,16 @@ static int plan_resident(snn_net *net)
             I.load += (double)w * word_load(S);
             if (S.kind != kPoisson && reads_neurons(S)) I.read_load += (double)w * word_load(S);
             step_kernels += 0.0025 * (double)w * (S.kind == kHH ? 1.0 : 0.3);
+            bool delivers = false;
+            for (int o = 0; o < S.n_out; ++o) delivers |= net->projs[S.out_proj[o]].nnz > 0;
+            if (delivers) I.rows += spikes_per_step(S);
+            double got = 0.0;
+            for (int q = 0; q < S.n_in; ++q) {
+                const Proj &P = net->projs[S.in_proj[q]];
+                got += (double)P.nnz * spikes_per_step(net->segs[P.pre_seg]) / (double)std::max(P.n_pre, 1);
+            }
+            synapses += got;
+            most = std::max(most, got / (double)std::max(S.n, 1));
         }
         for (size_t k = 0; k < net->proj_of[b].size(); ++k) {
             const Proj &P = net->projs[net->proj_of[b][k]];
@@ -1832,6 +1854,7 @@ static int plan_resident(snn_net *net)
         }
         if (I.n_words == 0 || I.n_words > ((int64_t)1 << 20) || I.nnz >= ((int64_t)1 << 31)) return SNN_OK;
     }
+    step_kernels += std::max(1e-4 * synapses, 0.04 * most);
 
     // words of segment `s` held by each block of its cluster
     struct Layout {
@@ -1901,7 +1924,8 @@ static int plan_resident(snn_net *net)
                 L.lds.push_back(8 * g[r] + (kResNeuronRec + 2560 + ((feat & kFeatRec) ? 512 : 0)) * st[r] +
                                 kResSourceRec * po[r] + 28 * I.n_words + 4 * kResList + (int64_t)sizeof(ResFeed) * feeds[r]);
                 worst_lds = std::max(worst_lds, L.lds.back());
-                worst = std::max(worst, 2.0 + 4.0 * std::ceil((double)st[r] / 16.0));
+                worst = std::max(worst, 2.0 + 4.0 * std::ceil((double)st[r] / 16.0) +
+                                            std::max(0.0, 0.001 * (double)I.n_words + 0.014 * I.rows - 1.0));
             }
             L.blocks += M;
         }

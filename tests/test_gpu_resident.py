@@ -306,7 +306,7 @@ def test_even_calls_keep_the_words_they_begin_with(snn, name):
 
 def singles():
     """More networks than compute units, each in a block of its own."""
-    base = layered(1, 70, 200, 20)["instances"][0]
+    base = layered(1, 70, 500, 20)["instances"][0]
     return dict(dt=0.1, substeps=3, instances=[dict(base, seed=netgen.instance_seed(11, i)) for i in range(300)])
 
 
@@ -462,3 +462,30 @@ def test_tags_begin_anew(snn):
         got.append(everything(net, spec))
         net.close()
     assert not differing(*got)
+
+
+def sources_onto(a, b, rate, n=1, p=None):
+    base = netgen.layered_instance(np.random.default_rng(3), a, b, 10, rate_hz=rate, p_ab=p or min(0.5, 2e6 / a / b),
+                                   p_bc=0.5)
+    return dict(dt=0.1, substeps=3, instances=[dict(base, seed=netgen.instance_seed(3, i)) for i in range(n)])
+
+
+@pytest.mark.parametrize("make,want", [
+    (lambda: sources_onto(100000, 1000, 200.0), False),       # each block would walk 2 000 rows a step
+    (lambda: sources_onto(300000, 64, 20.0), False),
+    (lambda: sources_onto(20000, 1000, 20.0), True),
+    (lambda: sources_onto(5000, 1000, 1000.0), True),         # rows of 400 synapses
+    (lambda: sources_onto(5000, 100, 1000.0, n=40), True),
+    (lambda: layered(1, 100, 1000, 100, 1.0), True),
+    (singles, True)])
+def test_networks_that_run_resident(snn, make, want):
+    """Networks whose sources' deliveries outweigh the shorter chain keep the
+    step kernels, which spread them over the chip."""
+    import torch
+    print("case: resident choice", flush=True)
+    spec = make()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        net = snn.Network(spec, stream=stream)
+        assert steps_resident(snn, net, stream) == want
+        net.close()
