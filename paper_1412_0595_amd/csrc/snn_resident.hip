@@ -442,6 +442,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
     share(r_begin, r_end, help_i, help_n);
     // the next step whose starting state is also left as a checkpoint
     int64_t next_ckpt = a.ckpt_every > 0 ? (t0 / a.ckpt_every + 1) * a.ckpt_every : -1;
+    const int64_t t_all = multi ? t0 : t0 - 1;   // every word is read up to this step, see below
     // (step t0 - 1 has only the part that follows its update)
     for (int64_t t = t0 - 1;; ++t) {
         // ---- the block's neurons up to the voltage after the step, one word
@@ -563,7 +564,7 @@ __global__ __launch_bounds__(1024) void k_resident(ResArgs a)
         // a step ahead, go there after the last step.
         sources(t + 1);
         if (help_i >= 0) {
-            const bool all = t < t0 || (multi && (late_feeds || t == t0 || (t & (kResCheck - 1)) == 0));
+            const bool all = t <= t_all || (multi && (late_feeds || (t & (kResCheck - 1)) == 0));
             list_rows(t, all ? r_begin : e_begin, all ? r_end : e_end);
         }
         __syncthreads();
