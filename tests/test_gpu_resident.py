@@ -489,3 +489,63 @@ def test_networks_that_run_resident(snn, make, want):
         net = snn.Network(spec, stream=stream)
         assert steps_resident(snn, net, stream) == want
         net.close()
+
+
+def mixed(seed):
+    """Instances of populations of all kinds in any order and size, with
+    several, no or empty projections, and a step of any length."""
+    rng = np.random.default_rng([seed, 9])
+    instances = []
+    for i in range(rng.integers(1, 4)):
+        pops, projs = [], []
+        kinds = rng.permutation(["poisson", "hh", *rng.choice(["hh", "izh", "poisson"], rng.integers(1, 4))])
+        for k, kind in enumerate(kinds):
+            n = int(rng.choice([1, 63, 64, 65, 130, rng.integers(2, 900)]))
+            pop = dict(name=f"{kind}{k}", kind=str(kind), n=n, rate_hz=float(rng.choice([0.0, 50.0, 2000.0])) if kind == "poisson" else 0.0,
+                       i_ext=float(rng.choice([0.0, 0.2])) if kind == "hh" else 0.0)
+            if kind == "izh":
+                pop["abcd"] = netgen.izhikevich_params(rng, n, 0)
+            pops.append(pop)
+        for post, pop in enumerate(pops):
+            if pop["kind"] == "poisson":
+                continue
+            for pre in rng.permutation(len(pops))[:rng.integers(0, 5)]:
+                rp, ci = netgen.bernoulli_csr(rng, pops[pre]["n"], pop["n"], float(rng.choice([0.0, 0.02, 0.3, 1.0])))
+                projs.append(dict(pre=int(pre), post=post, row_ptr=rp, col_idx=ci, g=netgen.uniform_weights(rng, ci.size, 0.02),
+                                  e_rev=float(rng.choice([0.0, -92.0])), tau=float(rng.choice([1.0, 5.0])), stdp=None))
+        instances.append(dict(g_scale=float(rng.choice([0.3, 1.0, 4.0])), seed=seed * 10 + i, pops=pops, projs=projs))
+    return dict(dt=float(rng.choice([0.02, 0.1])), substeps=int(rng.choice([1, 2, 3, 5])), instances=instances)
+
+
+@pytest.mark.parametrize("seed", range(16))
+def test_mixed_networks(snn, seed):
+    """All forms that a network can take, with voltages that run away and
+    that are not numbers among them."""
+    print(f"case: resident mixed {seed}", flush=True)
+    spec = mixed(seed)
+    rng = np.random.default_rng([seed, 10])
+    state = {}
+    for b, inst in enumerate(spec["instances"]):
+        for p, pop in enumerate(inst["pops"]):
+            if pop["kind"] == "hh":
+                v = rng.uniform(-90.0, 40.0, pop["n"])
+                odd = rng.random(pop["n"]) < 0.05
+                v[odd] = rng.choice([250.0, -1500.0, 3e38, np.nan, -52.0, -25.0], odd.sum())
+                state[b, p] = v
+
+    recorded = [f"hh{k}" for k in range(5)] if seed % 2 else []
+
+    def run(mode):
+        net = snn.Network(spec, record_vbar=recorded)
+        if mode:
+            net.set_launch(**mode)
+        for (b, p), v in state.items():
+            net.set_state(b, p, snn.V, v)
+        for n in (5, 40, 1, 33, 8, 2, 12):
+            net.step(n)
+        out = everything(net, spec) + ([net.vbar_sum(b, p) for b, p in state] if recorded else [])
+        net.close()
+        return out
+    got = run(None)
+    for mode in (dict(mode=0), dict(mode=2)):
+        assert not differing(got, run(mode)), mode
