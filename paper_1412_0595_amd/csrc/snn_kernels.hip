@@ -1546,7 +1546,10 @@ hipError_t launch_check_weights(const float *w, const Proj *projs, int32_t n_pro
 {
     if (n_projs == 0 || max_nnz == 0) return hipSuccess;
     const int64_t bx = std::min<int64_t>((max_nnz + 2047) / 2048, 512);
-    hipLaunchKernelGGL(k_check_weights, dim3((unsigned)bx, (unsigned)n_projs), dim3(256), 0, s, w, projs, flag, wmax);
+    constexpr int32_t kRows = 32768;   // (a grid's second dimension is 16 bits)
+    for (int32_t q = 0; q < n_projs; q += kRows)
+        hipLaunchKernelGGL(k_check_weights, dim3((unsigned)bx, (unsigned)std::min(n_projs - q, kRows)), dim3(256), 0, s, w,
+                           projs + q, flag, wmax + q);
     return hipGetLastError();
 }
 

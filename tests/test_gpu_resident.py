@@ -549,3 +549,36 @@ def test_mixed_networks(snn, seed):
     got = run(None)
     for mode in (dict(mode=0), dict(mode=2)):
         assert not differing(got, run(mode)), mode
+
+
+def test_scales_of_many_projections(snn):
+    """g_scale and weights of a batch of more projections than the second
+    dimension of a grid holds, the last of them with the largest weight."""
+    import torch
+    print("case: many projections", flush=True)
+    rp, ci = np.array([0, 1], np.int32), np.zeros(1, np.int32)
+    pops = [dict(name=f"P{k}", kind="hh", n=1, rate_hz=0.0, i_ext=0.0) for k in range(8)]
+    projs = [dict(pre=(p + k) % 8, post=p, row_ptr=rp, col_idx=ci, g=np.array([0.01], np.float32), e_rev=0.0, tau=1.0,
+                  stdp=None) for p in range(8) for k in range(4)]
+    last = [dict(q) for q in projs]
+    last[-1]["g"] = np.array([2.0], np.float32)
+    n = 65536 // len(projs) + 2
+    spec = dict(dt=0.1, substeps=3, instances=[dict(g_scale=1.0, seed=i, pops=pops, projs=projs if i < n - 1 else last)
+                                               for i in range(n)])
+    net = snn.Network(spec)
+    scales = np.ones(n, np.float32)
+    net.set_gscale(scales)
+    w = torch.empty(net.weight_count, dtype=torch.float32, device="cuda")
+    net.get_weights_device(w)
+    assert float(w[-1]) == 2.0
+    net.set_weights_device(w)
+    # a scale that only the last projection's weight makes too large
+    scales[:] = 1e4
+    scales[-1] = 1.0
+    net.set_gscale(scales)
+    scales[-1] = 1e4
+    with pytest.raises(snn.SNNError) as e:
+        net.set_gscale(scales)
+    assert e.value.code == snn.SNN_ERANGE
+    net.step(3)
+    net.close()
