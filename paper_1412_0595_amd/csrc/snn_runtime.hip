@@ -286,7 +286,8 @@ struct snn_net {
 
 namespace {
 
-constexpr size_t kStageBytes = 256 << 10;   // largest read through pinned memory
+constexpr size_t kStageBytes = 256 << 10;   // largest read of two arrays through pinned memory, and
+constexpr size_t kStageOne = 16 << 10;      // of one
 
 void *dev_alloc(snn_net *net, size_t bytes)
 {
@@ -714,13 +715,15 @@ int proj_index(const snn_net *net, int32_t inst, int32_t proj)
 // Reads two device arrays (the second may be empty) once the stream has
 // finished.  A kernel writes small ones into pinned host memory: a copy to
 // pageable memory goes through the runtime's own staging (the spikes of 100
-// neurons: 22.0 us a call, here 13.6), and a state variable's two arrays come
-// in one (42.1 -> 13.6).
+// neurons: 22.0 us a call, here 12.7), and a state variable's two arrays come
+// in one (42.1 -> 12.9; of 30 000 neurons 38.5 -> 33.0).  Beyond 16 KiB the
+// runtime's copy of one array is the faster (18 000 bytes: 11.4 and 14.6 us,
+// 16 000: 22.7 and 14.4).
 int d2h(snn_net *net, void *dst, const void *src, size_t bytes, void *dst2 = nullptr, const void *src2 = nullptr,
         size_t bytes2 = 0)
 {
     if (bytes + bytes2 == 0) return SNN_OK;
-    if (net->h_stage && bytes + bytes2 <= kStageBytes && (bytes | bytes2) % 4 == 0) {
+    if (net->h_stage && bytes + bytes2 <= (bytes2 ? kStageBytes : kStageOne) && (bytes | bytes2) % 4 == 0) {
         std::lock_guard<std::recursive_mutex> hold(net->read_lock);
         HIP_OK(launch_read_words((const uint32_t *)src, (int64_t)(bytes / 4), (const uint32_t *)src2, (int64_t)(bytes2 / 4),
                                  (uint32_t *)net->d_stage, net->stream));
