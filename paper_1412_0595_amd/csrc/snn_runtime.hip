@@ -139,6 +139,7 @@ struct HostProj {            // host copy of what state access needs
 struct ResidentPlan {
     bool ok;                 // the tables are there: the network fits and is expected to step faster this way
     bool on;                 // used by the steps (off while the tuner measures the step kernels)
+    bool stale;              // d_syn holds older weights than the pool
     int blocks, block;
     size_t lds;
     bool together;           // some cluster has several blocks: all must be resident (cooperative launch)
@@ -599,6 +600,10 @@ int run_resident(snn_net *net, int64_t n, uint64_t *raster, int32_t raster_steps
     const int64_t ckpt_end = net->t + n;
     int rc = pending_to_bits(net);
     if (rc) return rc;
+    if (net->res.stale)
+        HIP_OK(launch_resident_fill(net->res.d_blocks, net->res.blocks, net->res.d_sources, net->d_col, net->d_w,
+                                    net->res.d_bounds, net->res.d_from, net->res.d_syn, net->stream));
+    net->res.stale = false;
     const NeuronArgs na = neuron_args(net);
     ResArgs a{};
     a.segs = net->d_segs;
@@ -2760,12 +2765,10 @@ int snn_set_weights_device(snn_net *net, const float *src)
             return fail(SNN_ERANGE, "projection %zu: g_scale * column sum / (1 - decay) exceeds %g uS", q, kGLimit);
     }
     HIP_OK(hipMemcpyAsync(net->d_w, src, 4 * (size_t)net->w_count, hipMemcpyDeviceToDevice, net->stream));
-    // the copies that the steps use; tile mode's when its kernels run
+    // the copies that tile mode and resident steps use: when those run
     net->pull_stale = true;
     if (net->launch.mode == kModeTiles && !net->res.on && (rc = refresh_pull(net))) return rc;
-    if (net->res.on)
-        HIP_OK(launch_resident_fill(net->res.d_blocks, net->res.blocks, net->res.d_sources, net->d_col, net->d_w,
-                                    net->res.d_bounds, net->res.d_from, net->res.d_syn, net->stream));
+    net->res.stale = true;
     if (net->launch.mode != kModeFused || net->pend_bits) return SNN_OK;
     // fused mode: the pending deliveries of S(t-1) were made with the old
     // weights; the other modes deliver them at step t with the new ones
