@@ -552,6 +552,11 @@ constexpr int64_t kTapeBytes = (int64_t)512 << 20, kTapeSteps = 32768;
 // waits: 30 and 8, 36 and 25, 40 and 38; 32 and 11, 42 and 31, 47 and 44; 37
 // and 16, 54 and 48, 62 and 66; 20 and 14, 37 and 40, 46 and 56.
 constexpr int64_t kResidentMin = 4;
+// The same for a recorded forward pass, among the launches of a training step
+// (cooperative launches have a queue of their own, and each change of queue
+// costs): forward and backward of 1 100 neurons, resident and not, 4 steps 98
+// and 80 us, 5 steps 102 and 92, 8 steps 111 and 113.
+constexpr int64_t kResidentRecord = 8;
 // Steps in a call that are launched kernel by kernel: a graph's replay costs
 // 10 to 15 us more than its kernels where the call is waited for (1 100
 // neurons, one step 32 and 20 us, three 40.6 and 35.9, four 49 and 49.5).
@@ -2872,7 +2877,7 @@ int snn_forward_record(snn_net *net, int32_t pop, int64_t n_steps, int32_t ckpt_
     na.raster = net->d_rec_raster;
     na.raster_steps = (int32_t)T;
     const PropArgs pa = prop_args(net);
-    const bool resident = use_resident(net, T);
+    const bool resident = T >= kResidentRecord && use_resident(net, T);
     if (!resident && (rc = materialize(net))) return rc;
     for (int64_t t = 0; t < T; ++t) {
         if (t % K == 0) {
