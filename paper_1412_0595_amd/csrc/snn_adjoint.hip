@@ -230,19 +230,27 @@ __global__ __launch_bounds__(64) void k_adj_states(AdjArgs a)
 
 // ---------------------------------------------------------------------------
 // Reverse the group: a block takes kRevNeurons loss neurons, the last steps
-// first, kRevSteps at a time.  A thread per (step, neuron) carries the
+// first, as many at a time as it has threads for.  A thread per (step, neuron) carries the
 // derivatives of the state after the step by the state before it (4 x 4) and
 // by the injected current through the substeps, into LDS; then a lane per
 // neuron follows the chain of the adjoint (lv, lm, lh, ln) through the steps.
 // The derivatives are most of the arithmetic and independent of each other;
 // the chain is 20 multiply-adds a step.  About 200 VGPRs, two wavefronts per
 // SIMD: blocks of four, so that one's chain runs beside the other's maps.
+// Eight neurons by 32 steps keep the most chains apart; a group of up to 8 or
+// 4 steps would leave most of such a block idle, so it takes 32 or 64 neurons
+// by as many steps (backward of 300 networks with 100 loss neurons each: one
+// step 93.5 -> 42.0 us, four 110 -> 53.7, five 116 -> 68.3); 32 only where that
+// leaves blocks for the chip (100 loss neurons, five steps: 37 us by 8, 42 by
+// 32; 4 000: 50 either way).
 // ---------------------------------------------------------------------------
-constexpr int kRevNeurons = 8, kRevSteps = 32, kRevMap = 21;
+constexpr int kRevThreads = 256, kRevMap = 21, kRevWide = 4096;
 
-__global__ __launch_bounds__(kRevNeurons * kRevSteps) void k_adj_reverse(AdjArgs a)
+template <int kRevNeurons>
+__global__ __launch_bounds__(kRevThreads) void k_adj_reverse(AdjArgs a)
 {
     extern __shared__ double s_map[];      // [step][entry][neuron]
+    constexpr int kRevSteps = kRevThreads / kRevNeurons;
     const int64_t N = a.n_loss;
     const int nn = threadIdx.x % kRevNeurons, st = threadIdx.x / kRevNeurons;
     const int64_t c = (int64_t)blockIdx.x * kRevNeurons + nn;
@@ -426,12 +434,16 @@ hipError_t launch_adj_group(const AdjArgs &a, int max_inc, hipStream_t s)
                        s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t lds = sizeof(double) * kRevNeurons * kRevSteps * kRevMap;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_adj_reverse), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds);
+    const size_t lds = sizeof(double) * kRevThreads * kRevMap;
+    auto reverse = [&](auto kernel, int neurons) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((a.n_loss + neurons - 1) / neurons)), dim3(kRevThreads), lds, s, a);
+    };
+    if (a.K <= kRevThreads / 64) reverse(k_adj_reverse<64>, 64);
+    else if (a.K <= kRevThreads / 32 && a.n_loss >= kRevWide) reverse(k_adj_reverse<32>, 32);
+    else reverse(k_adj_reverse<8>, 8);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adj_reverse, dim3((unsigned)((a.n_loss + kRevNeurons - 1) / kRevNeurons)),
-                       dim3(kRevNeurons * kRevSteps), lds, s, a);
     if (a.n_gitems > 0) hipLaunchKernelGGL(k_adj_gather, dim3((unsigned)a.n_gitems), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -281,3 +281,36 @@ def test_long_segment_matches_fp64_oracle(snn):
         say(f"    projection {q}: |dg gpu - oracle| / |dg oracle| = {rel:.2e}")
         assert rel <= 1e-3
     net.close()
+
+
+@pytest.mark.parametrize("T", [2, 4, 5, 8, 9])
+def test_recordings_of_a_few_steps(snn, T):
+    """Backward passes of a few steps, in the shapes of the reversal's blocks:
+    a batch of 4 500 loss neurons against its first network alone, bitwise,
+    and that against the oracle, bounds as above."""
+    import torch
+    say(f"case: adjoint, {T} steps")
+    base = netgen.layered_instance(np.random.default_rng(2), 200, 100, 5, rate_hz=2000.0, p_ab=0.3, p_bc=0.5)
+    insts = [dict(base, seed=netgen.instance_seed(2, i)) for i in range(45)]
+    dv = np.random.default_rng(3).normal(size=4500)
+    got = []
+    for n in (45, 1):
+        spec = dict(dt=0.1, substeps=3, instances=insts[:n])
+        net = snn.Network(spec, record_vbar=("B",))
+        vb = net.forward_record(1, T, T).cpu().numpy()
+        dg, ds, bad = net.backward(torch.tensor(dv[:100 * n], device=net.device), check=True)
+        assert bad == 0
+        got.append((vb[:100], dg[:net.weight_count // n].cpu().numpy(), float(ds[0])))
+        if n == 1:
+            ro, ri = _oracle_raster(net, spec, 0, T)
+        net.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert abs(got[0][2] - got[1][2]) <= 1e-12 * abs(got[1][2])
+    orc = O.OracleNet(insts[0])
+    for p in (1, 2):
+        orc.set_replay(p, ro, ri, T)
+    vb_o, grads, ds_o = orc.adjoint(T, 1, dv[:100])
+    g = got[1][1][:grads[0].size].astype(np.float64)
+    assert np.max(np.abs(vb_o - got[1][0])) < 1e-3
+    assert np.linalg.norm(g - grads[0]) <= 1e-3 * np.linalg.norm(grads[0]) and np.any(grads[0] != 0.0)
+    assert abs(got[1][2] - ds_o) <= 1e-3 * abs(ds_o)
