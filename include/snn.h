@@ -217,8 +217,9 @@ int snn_create(const snn_config *cfg, snn_net **out);
 void snn_destroy(snn_net *net);
 
 /* Enqueue n_steps timesteps on the net's stream and return (asynchronous; a
- * network whose state fits in LDS and that has no plastic projection steps
- * many times per launch, until snn_set_launch asks for the step kernels).  A
+ * network whose state fits in LDS and that has no plastic projection takes the
+ * steps of a call in one launch, but for calls of one to three steps, until
+ * snn_set_launch asks for the step kernels).  A
  * stream capture does not record the steps: they run at once, or are refused
  * (SNN_EINVAL) after steps that ran many to a launch.  One step is
  * the per-timestep update of Section 2 (Hodgkin-Huxley neurons integrated
@@ -309,7 +310,8 @@ int snn_get_weights(snn_net *net, int32_t inst, int32_t proj, float *out);
 int snn_memory_bytes(const snn_net *net, int64_t *per_proj_bytes);
 
 /* Current / new launch shape of the step kernels, which run from a
- * snn_set_launch on; snn_set_launch validates the ranges above
+ * snn_set_launch on (the memory of the one-launch steps is then released);
+ * snn_set_launch validates the ranges above
  * (SNN_EINVAL, also for mode 2 on a network with plastic projections and for
  * mode 3 with prop_block above 512; the launch is then left as it was).  A
  * change of mode converts the work pending for the next step (delivers it

@@ -6,6 +6,8 @@
 //               (wave scan + LDS block offsets + one atomic per block) of the
 //               propagation work of the next step.  In fused mode the block
 //               instead delivers its own spikes' rows (fused_delivery).
+//               With kFeatRelay (after k_clear_work) it lays out the work of
+//               the last step's spike words instead.
 //  k_propagate_rows  (sparse activity) persistent grid, one wavefront per
 //               chunk of a spiking row; 64-bit atomics into G.  In grouped
 //               mode wavefronts first take groups of a few spiking rows of

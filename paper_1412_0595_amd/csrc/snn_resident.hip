@@ -22,8 +22,8 @@
 // neuron draw the sources (in short calls) and poll the words meanwhile.
 //
 // Time per step, step kernels -> here (2 000 steps a call): 1 100 neurons in 7
-// blocks 7.0 -> 3.2 us, 21 000 neurons in 96 blocks 10.1 -> 4.4, 325 networks of
-// 220 neurons 19.7 -> 5.0, 48 of 2 000 to 20 000 neurons 37 -> 18.  An
+// blocks 7.0 -> 3.1 us, 21 000 neurons in 96 blocks 10.1 -> 4.4, 325 networks of
+// 220 neurons 19.7 -> 5.0, 48 of 2 000 to 20 000 neurons 36 -> 19.  An
 // exchange takes 0.8 to 2 of these, one evaluation of the rates 0.6.
 #include <algorithm>
 

@@ -1827,8 +1827,8 @@ static int plan_resident(snn_net *net)
     };
     // a word's part of its block's time, in updates of 64 Traub-Miles neurons:
     // those that neurons project to receive more synapses and are on the
-    // longer chain (21 000 neurons: 5.6, 5.3 and 4.8 us a step with 0.5, 1.5
-    // and 3 more for them)
+    // longer chain (21 000 neurons: 4.9, 4.7 and 4.3 us a step with 0.5, 1.5
+    // and 3 more for them, a batch of 48 uneven networks 15.1, 12.6 and 12.5)
     auto word_load = [&](const Seg &S) {
         if (S.kind == kPoisson) return 0.3;
         return (S.kind == kHH ? 1.0 : 0.3) + (reads_neurons(S) ? 3.0 : 0.0);
@@ -1889,8 +1889,8 @@ static int plan_resident(snn_net *net)
             L.first.push_back((int)L.blocks);
             L.n.push_back(M);
             // blocks for the populations that read neurons (a batch of 48 uneven
-            // networks 13.3 us a step; 15.2 with those whose share does not
-            // fill a block mixed into the others)
+            // networks 12.5 us a step, 14.2 with them mixed into the others;
+            // 21 000 neurons 4.3 and 4.6)
             const int Mr = M < 4 || I.read_load <= 0.0 || I.read_load >= I.load - 0.3 * (double)I.n_poi - 0.5
                                ? 0
                                : std::min(M - 1, (int)std::ceil(M * I.read_load / I.load));
