@@ -557,10 +557,13 @@ constexpr int64_t kResidentMin = 4;
 // costs): forward and backward of 1 100 neurons, resident and not, 4 steps 98
 // and 80 us, 5 steps 102 and 92, 8 steps 111 and 113.
 constexpr int64_t kResidentRecord = 8;
-// Steps in a call that are launched kernel by kernel: a graph's replay costs
-// 10 to 15 us more than its kernels where the call is waited for (1 100
-// neurons, one step 32 and 20 us, three 40.6 and 35.9, four 49 and 49.5).
-constexpr int64_t kDirectSteps = 3;
+// Calls of up to so many steps and kernels are launched kernel by kernel: a
+// graph's replay costs 10 to 15 us more than its kernels where the call is
+// waited for (1 100 neurons, rows: one step 32 and 20 us, three 40.6 and 35.9,
+// four 49 and 49.5), until the launches, about 4 us of host time each, take
+// longer than the kernels (tile mode, three kernels a step: two steps as long
+// either way, three 66 and 70; with plastic projections, four: two 54 and 63).
+constexpr int64_t kDirectSteps = 3, kDirectKernels = 6;
 constexpr int64_t kResidentLaunch = 8192;  // steps in one launch at most
 constexpr int64_t kResidentDraw = 32;      // steps in a call whose sources are drawn ahead
 // Exchange tags compare as signed differences, and a slot of the ring may keep
@@ -587,6 +590,13 @@ bool capturing(const snn_net *net)
 bool use_resident(snn_net *net, int64_t n)
 {
     return net->res.on && n >= (net->pend_given ? 1 : kResidentMin) && !capturing(net);
+}
+
+bool use_direct(const snn_net *net, int64_t n)
+{
+    const int mode = net->launch.mode;
+    const int64_t kernels = mode == kModeFused ? 1 : mode == kModeTiles ? 3 + (net->plastic ? 1 : 0) : 2;
+    return n <= kDirectSteps && n * kernels <= kDirectKernels;
 }
 
 // The pending deliveries are from here on those of the spike words of
@@ -683,7 +693,7 @@ int run_steps(snn_net *net, int64_t n)
     int rc = materialize(net);
     if (rc) return rc;
     net->pend_delivered = false;
-    if (n <= kDirectSteps && !captured) {
+    if (use_direct(net, n) && !captured) {
         for (; n > 0; --n, ++net->t) HIP_OK(enqueue_step(net, net->stream));
         return SNN_OK;
     }
@@ -2616,7 +2626,7 @@ int snn_time_steps(snn_net *net, int64_t n_steps, double *out_ms)
     if (n_steps < 1 || !out_ms) return fail(SNN_EINVAL, "need n_steps >= 1 and an output");
     // capture the graph before the clock starts: host capture time is not step time
     if (!use_resident(net, n_steps) &&
-        ((rc = materialize(net)) || (n_steps > kDirectSteps && (rc = prepare_graphs(net, n_steps)))))
+        ((rc = materialize(net)) || (!use_direct(net, n_steps) && (rc = prepare_graphs(net, n_steps)))))
         return rc;
     double ms = 0.0;
     rc = timed_on_snapshot(net, [&]() { return run_steps(net, n_steps); }, &ms);
